@@ -125,7 +125,12 @@ typedef struct rp_opts {
                             0: sliced rows -- each tile's rows sorted by length
                             in slices of 64, one lane per row;
                             RP_SCHEDULE_SEGSCAN (-2): see below;
-                            -1 (default): tuned -- sliced rows and the lane
+                            -1 (default): by shape -- where most instances
+                            are too large for one LDS window and have no
+                            band, cells: row sums in LDS, the iterate staged
+                            panel by panel, each row summed in order (as by
+                            0 and 1; reported as lanes 0); otherwise tuned:
+                            sliced rows and the lane
                             counts from the mean row length and its two
                             neighbours are timed on a few sweeps the first
                             time a system of that shape is solved on the
@@ -180,7 +185,7 @@ typedef struct rp_solve_info {  /* one per instance */
                              of ||(I-A)^{-1}1|| has been computed              */
     int32_t status;       /* RP_OK or RP_ERR_* for this instance               */
     int32_t lanes;        /* layout the tiled sparse products used: lanes per
-                             row, or 0 for sliced rows                         */
+                             row, or 0 for sliced rows and cells               */
     int32_t panels;       /* sliced rows only: column panels the instance's
                              iterate was staged in (its block is too large for
                              one LDS window and has no band), 0 otherwise     */

@@ -229,6 +229,16 @@ struct SlicedSet {
   Sliced<T> v{};
 };
 
+// Cells of one (tile set, matrix) pair, built on first use.
+template <typename T>
+struct CellSet {
+  bool built = false, ok = false;
+  DBuf<int32_t> rec, step;
+  DBuf<uint32_t> ix;
+  DBuf<T> val;
+  Cells<T> v{};
+};
+
 struct Mat {
   DBuf<int32_t> rp, col;
   DBuf<uint16_t> c16;
@@ -271,6 +281,13 @@ struct rp_system {
   SlicedSet<double> sl64[2];
   SlicedSet<float> sl32[2];
   bool sliced = false;  // per call: tiled sweeps use the sliced rows
+  // cells: their own tiles (built where cells_pay), and the entries of the
+  // forward [0] and transposed [1] matrix
+  TileSet c64, c32;  // order: the tiles of the blocks' lists one after another
+  DBuf<int32_t> cblk64, cblk32;  // lists of the blocks: [cblk[b], cblk[b+1]) of order
+  CellSet<double> ce64[2];
+  CellSet<float> ce32[2];
+  bool cells = false;  // per call: tiled sweeps use the cells
   int jvariant = 0;     // per call, Jacobi: 1 in-place update, 2 segmented-scan row sums (row chunks)
   DBuf<int32_t> erow[2];  // row of every stored entry, forward [0] / transposed [1] (segmented scan)
   // strongly connected components of S_? (forward graph), per reduced row:
@@ -861,6 +878,154 @@ void build_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t w
   ts.tl.order = ts.order.p;
 }
 
+// Cells: tiles and lists of the blocks for at most `most` rows per tile.
+struct CellPlan {
+  std::vector<int64_t> per;       // rows per tile of each instance
+  std::vector<int32_t> order;     // tiles of the lists, one list after another
+  std::vector<int32_t> first;     // list of block b: [first[b], first[b+1]) of order
+  double time = 0.0;              // modelled time of the longest list (us)
+};
+
+// Time of a tile (us), fitted to sweeps over 8 M states in chains of 25,000 to
+// 200,000 (2 to 25 panels; within 8% of the measured ones): an entry with its
+// share of the rows costs 0.85 ns in FP64 and 0.55 ns in FP32 (a compute unit's
+// share of the memory rate), a panel 1.2 us (two barriers, the copy into LDS).
+double cell_tile_time(size_t width, double entries, int64_t cols) {
+  const int64_t pw = width == 4 ? cell_panel<float>() : cell_panel<double>();
+  return (width == 4 ? 0.55e-3 : 0.85e-3) * entries + 1.2 * (double)((cols + pw - 1) / pw) + 1.0;
+}
+
+CellPlan cell_plan(const rp_system* s, int cus, size_t width, int64_t most) {
+  constexpr int X = 8;  // XCDs: block b runs on XCD b mod 8
+  const int K = s->K;
+  CellPlan p;
+  p.per.assign(K, 0);
+  std::vector<int32_t> t0(K + 1, 0), idx;
+  std::vector<double> cost;
+  std::vector<double> icost(K, 0.0);
+  double total = 0.0;
+  for (int k = 0; k < K; k++) {
+    t0[k] = (int32_t)cost.size();
+    const int64_t rows = s->roff_h[k + 1] - s->roff_h[k];
+    if (rows == 0) continue;
+    const int64_t nt = (rows + most - 1) / most;
+    p.per[k] = ((rows + nt - 1) / nt + PAD - 1) / PAD * PAD;
+    for (int64_t r = 0; r < rows; r += p.per[k]) {
+      const double share = (double)std::min<int64_t>(p.per[k], rows - r) / (double)rows;
+      cost.push_back(cell_tile_time(width, (double)s->z_h[k] * share, rows));
+      icost[k] += cost.back();
+    }
+    total += icost[k];
+    idx.push_back(k);
+  }
+  t0[K] = (int32_t)cost.size();
+  // Instances, largest first, to the least loaded XCD (their tiles read the
+  // same panels, from one L2), the tiles past its fair share to the next.
+  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return icost[a] > icost[b]; });
+  std::array<double, X> load{};
+  std::array<std::vector<int32_t>, X> mine;
+  auto least = [&]() { return (int)(std::min_element(load.begin(), load.end()) - load.begin()); };
+  for (int k : idx) {
+    int x = least();
+    for (int32_t t = t0[k]; t < t0[k + 1]; t++) {
+      if (load[x] + cost[t] > 1.02 * total / X) x = least();
+      mine[x].push_back(t);
+      load[x] += cost[t];
+    }
+  }
+  // An XCD's tiles, largest first, each to its least loaded block.
+  std::vector<std::vector<int32_t>> lists((size_t)cus);
+  std::vector<double> bload((size_t)cus, 0.0);
+  for (int x = 0; x < X; x++) {
+    std::stable_sort(mine[x].begin(), mine[x].end(), [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
+    for (int32_t t : mine[x]) {
+      int best = x;
+      for (int b = x; b < cus; b += X)
+        if (bload[b] < bload[best]) best = b;
+      lists[best].push_back(t);
+      bload[best] += cost[t];
+    }
+  }
+  p.first.assign(1, 0);
+  for (const auto& l : lists) {
+    p.order.insert(p.order.end(), l.begin(), l.end());
+    p.first.push_back((int32_t)p.order.size());
+  }
+  p.time = *std::max_element(bload.begin(), bload.end());
+  return p;
+}
+
+// Whether the sweeps of values `width` bytes wide run on cells, and their
+// tiles.  The other layouts take 2.5 ns (FP64) or 1.7 ns (FP32) of a compute
+// unit per entry of an instance without a window (a gather from L2 each) and
+// 1.05 or 0.57 ns with a whole one, measured on the same 8 M states; cells are
+// used where their modelled sweep is shorter by a tenth, and not beside
+// banded instances, whose entries fall into few panels.  The rows per tile are
+// those of the shortest modelled sweep: fewer rows even out the blocks' lists,
+// more rows stage fewer panels.
+void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBuf<int32_t>& blk,
+                      const rp_system::TileSet& main, size_t width) {
+  const int K = s->K;
+  ts.ok = false;
+  if (s->npad <= 0 || !main.ok || ctx->cus < 8) return;
+  const int64_t pw = width == 4 ? cell_panel<float>() : cell_panel<double>();
+  double other = 0.0;
+  bool none = false;
+  for (int k = 0; k < K; k++) {
+    const int64_t rows = s->roff_h[k + 1] - s->roff_h[k];
+    if (rows == 0) continue;
+    const int32_t kind = main.kind_h[main.inst0_h[k]];
+    if (kind == WIN_BAND || rows >= pw << (30 - CELL_STEP_BITS)) return;
+    none = none || kind == WIN_NONE;
+    const double ns = kind == WIN_NONE ? (width == 4 ? 1.7 : 2.5) : (width == 4 ? 0.57 : 1.05);
+    other += 1e-3 * ns * (double)s->z_h[k] / (double)ctx->cus;
+  }
+  if (!none) return;
+  CellPlan plan;
+  for (int64_t most = CELL_ROWS; most >= CELL_ROWS / 2; most -= 1024) {
+    CellPlan p = cell_plan(s, ctx->cus, width, most);
+    if (plan.per.empty() || p.time < plan.time) plan = std::move(p);
+  }
+  if (plan.time > 0.9 * other) return;
+  std::vector<int32_t> trow0, tnr, tinst, tw0, tnw, tkind, tc0(K + 1, 0);
+  for (int k = 0; k < K; k++) {
+    tc0[k] = (int32_t)trow0.size();
+    const int64_t lo = s->roff_h[k], hi = s->roff_h[k + 1];
+    for (int64_t r = lo; r < hi; r += plan.per[k]) {
+      trow0.push_back((int32_t)r);
+      tnr.push_back((int32_t)std::min<int64_t>(plan.per[k], hi - r));
+      tinst.push_back(k);
+      tw0.push_back((int32_t)lo);
+      tnw.push_back((int32_t)(hi - lo));
+      tkind.push_back(WIN_NONE);
+    }
+  }
+  tc0[K] = (int32_t)trow0.size();
+  const int32_t nt = tc0[K];
+  dalloc(ctx, blk, plan.first.size());
+  to_dev(ctx, blk.p, plan.first.data(), plan.first.size());
+  dalloc(ctx, ts.row0, (size_t)nt);
+  dalloc(ctx, ts.nrows, (size_t)nt);
+  dalloc(ctx, ts.inst, (size_t)nt);
+  dalloc(ctx, ts.inst0, (size_t)K + 1);
+  dalloc(ctx, ts.w0, (size_t)nt);
+  dalloc(ctx, ts.nw, (size_t)nt);
+  dalloc(ctx, ts.kind, (size_t)nt);
+  dalloc(ctx, ts.order, (size_t)nt);
+  to_dev(ctx, ts.row0.p, trow0.data(), (size_t)nt);
+  to_dev(ctx, ts.nrows.p, tnr.data(), (size_t)nt);
+  to_dev(ctx, ts.inst.p, tinst.data(), (size_t)nt);
+  to_dev(ctx, ts.inst0.p, tc0.data(), (size_t)K + 1);
+  to_dev(ctx, ts.w0.p, tw0.data(), (size_t)nt);
+  to_dev(ctx, ts.nw.p, tnw.data(), (size_t)nt);
+  to_dev(ctx, ts.kind.p, tkind.data(), (size_t)nt);
+  to_dev(ctx, ts.order.p, plan.order.data(), (size_t)nt);
+  ts.kind_h = tkind;
+  ts.inst0_h = tc0;
+  ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, 0};
+  ts.ok = true;
+}
+
 // Resident Jacobi (one block per instance, many sweeps per launch) pays off
 // where a sweep is too small to spread over several CUs: every non-empty
 // instance's two iterates fit the LDS and its sweep moves at most
@@ -986,6 +1151,17 @@ rp_system::TileSet& tiles_for(rp_system* s) {
   return sizeof(T) == 4 ? s->t32 : s->t64;
 }
 
+template <typename T>
+rp_system::TileSet& cell_tiles_for(rp_system* s) {
+  return sizeof(T) == 4 ? s->c32 : s->c64;
+}
+
+// Tiles of this call's sweeps for values of type T.
+template <typename T>
+rp_system::TileSet& sweep_tiles(rp_system* s, bool cells) {
+  return cells ? cell_tiles_for<T>(s) : tiles_for<T>(s);
+}
+
 // Whether this call runs the LDS-staged tile kernels for values of type T.
 template <typename T>
 bool tiled(rp_system* s) {
@@ -1003,6 +1179,49 @@ template <>
 SlicedSet<double>& sliced_for<double>(rp_system* s, bool tr) { return s->sl64[tr ? 1 : 0]; }
 template <>
 SlicedSet<float>& sliced_for<float>(rp_system* s, bool tr) { return s->sl32[tr ? 1 : 0]; }
+
+template <typename T>
+CellSet<T>& cells_for(rp_system* s, bool tr);
+template <>
+CellSet<double>& cells_for<double>(rp_system* s, bool tr) { return s->ce64[tr ? 1 : 0]; }
+template <>
+CellSet<float>& cells_for<float>(rp_system* s, bool tr) { return s->ce32[tr ? 1 : 0]; }
+
+// Cells of the forward or transposed matrix, built once; false when the
+// system's shape does not run on cells or the steps hold fewer than
+// kCellStepEntries entries each (a hub row's are taken one at a time).
+constexpr int kCellStepEntries = 16;
+template <typename T>
+bool ensure_cells(rp_context* ctx, rp_system* s, bool tr) {
+  CellSet<T>& cs = cells_for<T>(s, tr);
+  rp_system::TileSet& ts = cell_tiles_for<T>(s);
+  if (!ts.ok || !s->tiles_on) return false;
+  if (cs.built) return cs.ok;
+  if (tr) ensure_transpose(ctx, s);
+  const MatView<T> m = view<T>(s, tr);
+  const DBuf<int32_t>& blk = sizeof(T) == 4 ? s->cblk32 : s->cblk64;
+  const int64_t nlist = (int64_t)ts.tl.ntile * CELL_WAVES;
+  DBuf<int32_t> count, base, scan_tmp, unit;
+  dalloc(ctx, count, (size_t)nlist);
+  dalloc(ctx, base, (size_t)nlist + 1);
+  dalloc(ctx, scan_tmp, scan_scratch_elems(nlist));
+  dalloc(ctx, unit, (size_t)ts.tl.ntile);
+  HIPCHK(ctx, launch_cells_count<T>(ctx->stream, m, ts.tl, count.p, unit.p));
+  HIPCHK(ctx, launch_scan(ctx->stream, count.p, base.p, nlist, scan_tmp.p));
+  const int32_t nstep = read_i32(ctx, base.p + nlist);
+  cs.built = true;
+  // (a step adds 64 entries, unless rows have many entries in one panel)
+  if ((int64_t)nstep > s->z / kCellStepEntries) return false;
+  dalloc(ctx, cs.step, (size_t)nstep);
+  dalloc(ctx, cs.val, (size_t)s->z + 1);
+  dalloc(ctx, cs.ix, (size_t)s->z + 1);
+  dalloc(ctx, cs.rec, (size_t)ts.tl.ntile * CR_WORDS);
+  HIPCHK(ctx, launch_cells_fill<T>(ctx->stream, m, ts.tl, ts.order.p, base.p, unit.p, cs.step.p, cs.val.p, cs.ix.p,
+                                   cs.rec.p));
+  cs.v = Cells<T>{cs.rec.p, blk.p, cs.step.p, cs.val.p, cs.ix.p, m.d, (int32_t)blk.n - 1};
+  cs.ok = true;
+  return true;
+}
 
 // Slice bytes above which a sweep streams them past the caches (the MI355X
 // last-level cache holds 256 MB; the vectors need room beside the matrix).
@@ -1279,7 +1498,7 @@ int first_batch(const InnerCfg& cfg) { return std::min(4, cfg.chunk); }
 // max_iter, or the sweep count not even).
 template <typename T>
 bool jacobi_graph_batches(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const InnerCfg& cfg, bool sl_on,
-                          int64_t& launched, std::vector<std::pair<int64_t, int64_t>>& batches) {
+                          bool ce_on, int64_t& launched, std::vector<std::pair<int64_t, int64_t>>& batches) {
   const int64_t B = cfg.chunk;
   if (!ctx->flag_h || B < 2 || B % 2 != 0 || launched % 2 != 0 || launched + B > cfg.max_iter) return false;
   hipStream_t st = ctx->stream;
@@ -1295,7 +1514,8 @@ bool jacobi_graph_batches(rp_context* ctx, rp_system* s, bool tr, const T* rhs, 
   dalloc(ctx, gseq, 1);
   HIPCHK(ctx, launch_set_i64(st, base.p, launched));
   HIPCHK(ctx, launch_set_i32(st, gseq.p, ctx->flag_seq));
-  Tiles tl = tiles_for<T>(s).tl;
+  const Cells<T> cev = ce_on ? cells_for<T>(s, tr).v : Cells<T>{};
+  Tiles tl = sweep_tiles<T>(s, ce_on).tl;
   tl.sbase = base.p;
   double* P0 = s->tp.p;
   double* P1 = s->tp.p + tl.ntile;
@@ -1310,7 +1530,9 @@ bool jacobi_graph_batches(rp_context* ctx, rp_system* s, bool tr, const T* rhs, 
     T* xn = (i & 1) ? w.xa.p : w.xb.p;
     double* pcur = (i & 1) ? P1 : P0;
     const double* pprev = (i & 1) ? P0 : P1;
-    e = sl_on ? launch_jacobi_sliced<T>(cs, slv, rhs, x, xn, tl, i, pprev, pcur, s->status_in.p, s->iters_in.p,
+    e = ce_on ? launch_jacobi_cells<T>(cs, cev, rhs, x, xn, tl, i, pprev, pcur, s->status_in.p, s->iters_in.p,
+                                       s->meas_in.p, s->thr_in.p, cfg.strict, cfg.max_iter, ndone, wd)
+      : sl_on ? launch_jacobi_sliced<T>(cs, slv, rhs, x, xn, tl, i, pprev, pcur, s->status_in.p, s->iters_in.p,
                                         s->meas_in.p, s->thr_in.p, cfg.strict, cfg.max_iter, ndone, wd)
               : launch_jacobi_tile<T>(cs, s->L, m, rhs, x, xn, tl, i, pprev, pcur, s->status_in.p, s->iters_in.p,
                                       s->meas_in.p, s->thr_in.p, cfg.strict, cfg.max_iter, ndone, wd);
@@ -1379,7 +1601,9 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
                                s->sbest_it.p, kStallWindow, ndone));
   };
   // tiled sweeps on sliced rows when this call chose them
-  const bool sl_on = s->sliced && tiled<T>(s) && ensure_sliced<T>(ctx, s, tr);
+  const bool ce_on = s->cells && tiled<T>(s) && ensure_cells<T>(ctx, s, tr);
+  const Cells<T> cev = ce_on ? cells_for<T>(s, tr).v : Cells<T>{};
+  const bool sl_on = !ce_on && s->sliced && tiled<T>(s) && ensure_sliced<T>(ctx, s, tr);
   const Sliced<T> slv = sl_on ? sliced_for<T>(s, tr).v : Sliced<T>{};
   const int kJ = std::is_same<T, float>::value ? RP_PROF_JACOBI_FP32 : RP_PROF_JACOBI_FP64;
   const int kT = std::is_same<T, float>::value ? RP_PROF_JACOBI_TAIL_FP32 : RP_PROF_JACOBI_TAIL_FP64;
@@ -1432,7 +1656,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
     if (jv == 0 && tiled<T>(s)) {
       // LDS-staged sweeps; the decision on sweep j is taken inside sweep j+1
       // (or by the check kernel after the last sweep of a batch)
-      const Tiles& tl = tiles_for<T>(s).tl;
+      const Tiles& tl = sweep_tiles<T>(s, ce_on).tl;
       double* P0 = s->tp.p;
       double* P1 = s->tp.p + tl.ntile;
       std::vector<std::pair<int64_t, int64_t>> batches;
@@ -1441,7 +1665,11 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
         T* xn = (j & 1) ? w.xa.p : w.xb.p;
         double* pcur = (j & 1) ? P1 : P0;
         const double* pprev = (j & 1) ? P0 : P1;
-        if (sl_on)
+        if (ce_on)
+          HIPCHK(ctx, launch_jacobi_cells<T>(st, cev, rhs, x, xn, tl, j, pprev, pcur, s->status_in.p, s->iters_in.p,
+                                             s->meas_in.p, s->thr_in.p, cfg.strict, cfg.max_iter, ndone,
+                                             cfg.measmode == MEAS_WDELTA));
+        else if (sl_on)
           HIPCHK(ctx, launch_jacobi_sliced<T>(st, slv, rhs, x, xn, tl, j, pprev, pcur, s->status_in.p, s->iters_in.p,
                                               s->meas_in.p, s->thr_in.p, cfg.strict, cfg.max_iter, ndone,
                                               cfg.measmode == MEAS_WDELTA));
@@ -1458,7 +1686,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
       int batch = first_batch(cfg);
       int64_t ahead = 0;  // sweeps of the current batch launched ahead
       if (cfg.graph && !cfg.stall) {
-        if (jacobi_graph_batches<T>(ctx, s, tr, rhs, cfg, sl_on, launched, batches)) {
+        if (jacobi_graph_batches<T>(ctx, s, tr, rhs, cfg, sl_on, ce_on, launched, batches)) {
           prof_batches(ctx, s, kJ, batches, 4 + tb_, 4 + 4 * tb_);
           return launched;
         }
@@ -1506,7 +1734,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
             ts0_h.resize((size_t)tl.ntile + 1);
             to_host(ctx, ts0_h.data(), slv.t_s0, (size_t)tl.ntile + 1);
           }
-          if (build_tail(ctx, s, sizeof(T), st_h, tiles_for<T>(s), sl_on ? &ts0_h : nullptr)) {
+          if (build_tail(ctx, s, sizeof(T), st_h, sweep_tiles<T>(s, ce_on), sl_on ? &ts0_h : nullptr)) {
             tail = true;
             break;
           }
@@ -1520,7 +1748,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
         // in CSR order, which sums alike), so the iterates are those the tiled
         // sweeps would have produced
         const Tiles& tt = s->tail.tl;
-        const int lanes = sl_on ? 1 : s->L;
+        const int lanes = sl_on || ce_on ? 1 : s->L;
         std::vector<std::pair<int64_t, int64_t>> tb;
         while (launched < cfg.max_iter) {
           ProfSpan sp(ctx);
@@ -1593,7 +1821,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
     prof_batches(ctx, s, kB, batches, 2 * (4 + tb_), 8 + 21 * tb_);
   } else if (tiled<T>(s)) {
     // tiled BiCGStab: five launches per step, scalars reduced in-kernel
-    const Tiles& tl = tiles_for<T>(s).tl;
+    const Tiles& tl = sweep_tiles<T>(s, ce_on).tl;
     const int kB = std::is_same<T, float>::value ? RP_PROF_BICGSTAB_FP32 : RP_PROF_BICGSTAB_FP64;
     BicgState b{s->status_in.p, s->iters_in.p, s->meas_in.p, s->thr_in.p, s->rho2.p, s->alpha.p, s->omega.p,
                 ndone, cfg.measmode, cfg.max_iter};
@@ -1602,10 +1830,12 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
     std::vector<std::pair<int64_t, int64_t>> batches;
     auto bstep = [&](int64_t j) {
       HIPCHK(ctx, launch_bicg_p_tile<T>(st, w.r.p, w.p.p, w.v.p, tl, j, s->tpc.p, s->tps.p, b));
-      if (sl_on) HIPCHK(ctx, launch_spmv_sliced<T>(st, 0, slv, w.p.p, w.v.p, w.q.p, tl, s->status_in.p, s->tpa.p));
+      if (ce_on) HIPCHK(ctx, launch_spmv_cells<T>(st, 0, cev, w.p.p, w.v.p, w.q.p, s->status_in.p, s->tpa.p));
+      else if (sl_on) HIPCHK(ctx, launch_spmv_sliced<T>(st, 0, slv, w.p.p, w.v.p, w.q.p, tl, s->status_in.p, s->tpa.p));
       else HIPCHK(ctx, launch_spmv_tile<T>(st, s->L, 0, m, w.p.p, w.v.p, w.q.p, tl, s->status_in.p, s->tpa.p));
       HIPCHK(ctx, launch_bicg_s_tile<T>(st, w.r.p, w.v.p, w.s.p, tl, j, s->tpa.p, s->tps.p, b));
-      if (sl_on) HIPCHK(ctx, launch_spmv_sliced<T>(st, 1, slv, w.s.p, w.t.p, w.q.p, tl, s->status_in.p, s->tpb.p));
+      if (ce_on) HIPCHK(ctx, launch_spmv_cells<T>(st, 1, cev, w.s.p, w.t.p, w.q.p, s->status_in.p, s->tpb.p));
+      else if (sl_on) HIPCHK(ctx, launch_spmv_sliced<T>(st, 1, slv, w.s.p, w.t.p, w.q.p, tl, s->status_in.p, s->tpb.p));
       else HIPCHK(ctx, launch_spmv_tile<T>(st, s->L, 1, m, w.s.p, w.t.p, w.q.p, tl, s->status_in.p, s->tpb.p));
       HIPCHK(ctx, launch_bicg_xr_tile<T>(st, w.xa.p, w.p.p, w.s.p, w.r.p, w.t.p, w.q.p, tl, j, s->tpb.p, s->tpc.p,
                                          b));
@@ -1736,7 +1966,13 @@ void refine(rp_context* ctx, rp_system* s, bool tr, int method, const double* b6
     if (ctx->prof) to_host(ctx, sto.data(), s->status_out.p, K);
     // sliced rows when this call uses them and the FP64 slices exist
     const SlicedSet<double>& sl64 = sliced_for<double>(s, tr);
-    if (t64 && s->sliced && sl64.ok)
+    const CellSet<double>& ce64 = cells_for<double>(s, tr);
+    const bool on_cells = t64 && s->cells && ensure_cells<double>(ctx, s, tr);
+    const Tiles& t64l = sweep_tiles<double>(s, on_cells).tl;
+    if (on_cells)
+      PROF(ctx, RP_PROF_RESIDUAL_FP64,
+           launch_spmv_cells<double>(st, 2, ce64.v, s->x64.p, s->r64.p, b64, s->status_out.p, s->tpa.p));
+    else if (t64 && s->sliced && sl64.ok)
       PROF(ctx, RP_PROF_RESIDUAL_FP64,
            launch_spmv_sliced<double>(st, 2, sl64.v, s->x64.p, s->r64.p, b64, s->t64.tl, s->status_out.p, s->tpa.p));
     else if (t64)
@@ -1749,7 +1985,7 @@ void refine(rp_context* ctx, rp_system* s, bool tr, int method, const double* b6
       for (int k = 0; k < K; k++)
         if (sto[k] == ST_RUN)
           ctx->stat[RP_PROF_RESIDUAL_FP64].bytes += 12.0 * (double)s->z_h[k] + 36.0 * (double)s->nq_h[k];
-    HIPCHK(ctx, launch_fin_outer(st, t64 ? tile_chunks(s->t64.tl) : s->ch, t64 ? s->tpa.p : s->pa.p,
+    HIPCHK(ctx, launch_fin_outer(st, t64 ? tile_chunks(t64l) : s->ch, t64 ? s->tpa.p : s->pa.p,
                                  s->status_out.p, s->outer_it.p, s->rn.p, s->scale.p, tb, tol,
                                  certified ? 1 : 0, o.max_refine, s->thr_in.p, o.inner_tol, floor_rel, margin, s->rbest.p,
                                  s->stall.p, s->tot_it.p, max_iter, ndone_out));
@@ -1935,7 +2171,10 @@ void check_opts(rp_context* ctx, const rp_opts* o) {
   }
 }
 
-// Row layout of the tiled kernels, chosen by timing: the sliced rows (one
+constexpr int kLayoutCells = -3;  // tuned_layout: the cells
+
+// Row layout of the tiled kernels: the cells where the system's shape calls for
+// them (build_cell_tiles), else chosen by timing: the sliced rows (one
 // lane per row), and lane groups of the mean-row-length choice L and of its
 // neighbours L/2 and 2L, each run a few Jacobi sweeps (on the workspace,
 // never converging); a lane-group layout replaces the sliced rows only when
@@ -1945,6 +2184,7 @@ void check_opts(rp_context* ctx, const rp_opts* o) {
 template <typename T>
 int tuned_layout(rp_context* ctx, rp_system* s, bool tr) {
   if (!tiled<T>(s) || resident_for<T>(s).ok) return s->L;
+  if (ensure_cells<T>(ctx, s, tr)) return kLayoutCells;
   const std::array<int64_t, 5> key{s->npad, s->z, (int64_t)s->K, (int64_t)sizeof(T), tr ? 1 : 0};
   auto it = ctx->lane_choice.find(key);
   if (it != ctx->lane_choice.end()) return it->second;
@@ -2055,9 +2295,10 @@ void solve_core(rp_context* ctx, rp_system* s, bool tr, int method, const double
   if (layout == 0 && !(s->tiles_on && (f32 ? (tiled<float>(s) && ensure_sliced<float>(ctx, s, tr))
                                            : (tiled<double>(s) && ensure_sliced<double>(ctx, s, tr)))))
     layout = s->L;
+  s->cells = layout == kLayoutCells;
   s->sliced = layout == 0;
   if (layout > 0) s->L = layout;
-  log.lanes = s->sliced ? 0 : s->L;
+  log.lanes = s->sliced || s->cells ? 0 : s->L;
   log.panels.assign(K, 0);
   if (s->sliced) {
     const std::vector<int32_t>& np = f32 ? sliced_for<float>(s, tr).npan_h : sliced_for<double>(s, tr).npan_h;
@@ -2073,6 +2314,7 @@ void solve_core(rp_context* ctx, rp_system* s, bool tr, int method, const double
       s->L = L;
       s->tiles_on = true;
       s->sliced = false;
+      s->cells = false;
       s->jvariant = 0;
     }
   } restore{s, saved_L};
@@ -2321,7 +2563,10 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   build_tiles(ctx, s, s->t32, sizeof(float), 2, hist);
   build_resident(ctx, s, s->res64, sizeof(double));
   build_resident(ctx, s, s->res32, sizeof(float));
-  s->ntile_max = std::max(s->t64.ok ? s->t64.tl.ntile : 0, s->t32.ok ? s->t32.tl.ntile : 0);
+  build_cell_tiles(ctx, s, s->c64, s->cblk64, s->t64, sizeof(double));
+  build_cell_tiles(ctx, s, s->c32, s->cblk32, s->t32, sizeof(float));
+  for (const rp_system::TileSet* t : {&s->t64, &s->t32, &s->c64, &s->c32})
+    if (t->ok) s->ntile_max = std::max(s->ntile_max, t->tl.ntile);
   HIPCHK(ctx, hipStreamSynchronize(st));
 }
 

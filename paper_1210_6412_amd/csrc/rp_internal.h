@@ -122,6 +122,55 @@ struct PanelShape {
   static constexpr int MAXS = 16;
 };
 
+// Cells of one tile set and one matrix: the layout of batches whose instances
+// are mostly too large for one LDS window and have no band (uniformly spread
+// targets).  A tile is a range of an instance's rows.  Its block's first
+// CELL_WAVES wavefronts own cell_wave_rows consecutive rows each, whose sums
+// live in LDS; the other wavefronts, in two teams, stage the instance's iterate
+// into LDS panel by panel (pw columns at a time, the teams in turn).  A
+// wavefront's entries keep the positions its rows have in the CSR arrays,
+// ordered by panel, inside a panel by rank within the row (all first entries,
+// then all second ones, ...) and inside a rank by row, and are taken in steps of
+// at most 64 entries of one panel and rank: their rows differ, so the lanes add
+// their products to the sums at once without atomics, and a row's entries are
+// added in column order, as one lane per row would.  One block per compute unit takes a fixed list of tiles, the
+// first loads of the next under way before the last one's rows are written.
+constexpr int CELL_WAVES = 8;       // wavefronts of a block that add entries
+constexpr int CELL_TEAM = 4;        // wavefronts of one of the two staging teams
+constexpr int CELL_ROWS = 8192;     // most rows of a tile: LDS rows reserved for the sums
+constexpr int CELL_COL_BITS = 22;   // ix: row within the wavefront's rows (10 bits), column within
+                                    //     the panel
+constexpr int CELL_STEP_BITS = 8;   // step: panel, 1 bit set on the first step of a rank, number of
+                                    //     entries (7 bits; 0: past the list's end)
+constexpr int CELL_REGS = 16;       // 16-byte registers of a staging lane that hold a panel
+// Rows of the tile that each wavefront owns (a multiple of 16: whole 128-byte
+// lines of an FP64 vector).
+__host__ __device__ inline int cell_wave_rows(int nrows) {
+  return (nrows + 16 * CELL_WAVES - 1) / (16 * CELL_WAVES) * 16;
+}
+// Panel width: what a team's registers hold (with the sums, less than the LDS).
+template <typename T>
+constexpr int32_t cell_panel() {
+  return CELL_REGS * CELL_TEAM * 64 * 16 / (int)sizeof(T);
+}
+// A tile as its block reads it, in the order of the blocks' lists.
+enum : int { CR_ROW0, CR_NROWS, CR_LO, CR_COLS, CR_INST, CR_TILE, CR_T0, CR_T1, CR_UNIT, CR_ENTRY,
+             CR_STEP = CR_ENTRY + CELL_WAVES, CR_WORDS = 32 };
+// CR_ENTRY + w, CR_STEP + w: first entry of wavefront w's rows, its first step
+// (of all steps; CR_STEP + CELL_WAVES: the tile's end); CR_UNIT: 1 when every
+// diagonal entry of the tile's rows is 1
+static_assert(CR_STEP + CELL_WAVES < CR_WORDS, "tile record");
+template <typename T>
+struct Cells {
+  const int32_t* rec;   // [ntile * CR_WORDS]
+  const int32_t* blk;   // [nblk+1] tiles of block b: rec [blk[b], blk[b+1])
+  const int32_t* step;  // [nstep]
+  const T* val;         // [z+1]
+  const uint32_t* ix;   // [z+1]
+  const T* d;           // [npad] diagonal
+  int32_t nblk;
+};
+
 // Stopping measure of the inner iterations.
 enum : int32_t {
   MEAS_DELTA = 0,     // Jacobi: max |x' - x|
@@ -318,6 +367,22 @@ hipError_t launch_jacobi_sliced(hipStream_t st, Sliced<T> sl, const T* rhs, cons
 template <typename T>
 hipError_t launch_spmv_sliced(hipStream_t st, int mode, Sliced<T> sl, const T* u, T* y, const T* qv, Tiles tl,
                               const int32_t* status, double* part);
+// cells: the number of steps of every list (tile, wavefront) and the tiles'
+// unit flags; then (sbase: prefix sums of the counts) the steps, the entries in
+// cell order and the tile records, tile `order[i]` at place i
+template <typename T>
+hipError_t launch_cells_count(hipStream_t st, MatView<T> m, Tiles tl, int32_t* nstep, int32_t* unit);
+template <typename T>
+hipError_t launch_cells_fill(hipStream_t st, MatView<T> m, Tiles tl, const int32_t* order, const int32_t* sbase,
+                             const int32_t* unit, int32_t* step, T* val, uint32_t* ix, int32_t* rec);
+template <typename T>
+hipError_t launch_jacobi_cells(hipStream_t st, Cells<T> cl, const T* rhs, const T* x, T* xn, Tiles tl, int64_t s,
+                               const double* pprev, double* pcur, int32_t* status, int64_t* iters, double* meas,
+                               const double* thr, int strict, int64_t max_iter, int32_t* ndone, int weighted);
+// modes as launch_spmv_sliced
+template <typename T>
+hipError_t launch_spmv_cells(hipStream_t st, int mode, Cells<T> cl, const T* u, T* y, const T* qv,
+                             const int32_t* status, double* part);
 hipError_t launch_residual_tile(hipStream_t st, int L, MatView<double> m, const double* b, const double* x,
                                 double* r, Tiles tl, const int32_t* status, double* part);
 

@@ -2979,6 +2979,601 @@ template hipError_t launch_spmv_sliced<float>(hipStream_t, int, Sliced<float>, c
                                               Tiles, const int32_t*, double*);
 
 // ============================================================================
+// Cells (see Cells in rp_internal.h): row sums in LDS, the iterate staged into
+// LDS panel by panel.  For instances that fit no window and have no band.
+//
+// Without a window every entry gathers its x element from L2, a 128-byte line
+// for 8 bytes: 2.4 cycles of a compute unit's L1 per gather at best (257 G
+// gathers/s over the chip, measured), and the sliced sweep, one pass of a block
+// over its tile, adds the gathers' time to that of streaming the entries.  Here
+// a tile reads each line of its instance's x once, as part of a panel, whatever
+// the number of its entries; the entries stream meanwhile.  8 M states in chains
+// of 50,000 / 100,000 / 200,000 (us per sweep, sliced rows -> cells): FP64
+// 340 -> 145, 327 -> 168, 335 -> 218; FP32 206 -> 108, 231 -> 113, 229 -> 139.
+// The 256-chain batch of 1,000..200,000 states (9.6 M states, 41 M entries):
+// FP64 365 -> 205 (two lanes per row: 343), 4.1 TB/s of 12 z + 36 n; FP32
+// 230 -> 137.  What bounds them: the memory rate up to about ten panels (50,000
+// states in FP64: 4.8 TB/s), then the panels (1.2 us each: two barriers, the
+// copy to LDS, the adding wavefronts' latency).
+// ============================================================================
+
+// One wavefront per list (tile, wavefront): its rows 64 at a time
+// (CELL_LANE_ROWS per lane), the entries of each panel ranked in their rows.
+constexpr int CELL_LANE_ROWS = CELL_ROWS / CELL_WAVES / 64;
+template <typename T, bool FILL>
+__global__ __launch_bounds__(BS) void k_cells_build(MatView<T> m, Tiles tl, const int32_t* __restrict__ sbase,
+                                                    int32_t* __restrict__ nstep, int32_t* __restrict__ unit,
+                                                    int32_t* __restrict__ step, T* __restrict__ val,
+                                                    uint32_t* __restrict__ ix) {
+  constexpr int PW = cell_panel<T>();
+  const int list = blockIdx.x * (BS / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int c = list / CELL_WAVES, w = list % CELL_WAVES;
+  if (c >= tl.ntile) return;
+  const int nr = tl.nrows[c], rw = cell_wave_rows(nr), lo = tl.w0[c];
+  const int P = (tl.nw[c] + PW - 1) / PW;
+  const int r0 = tl.row0[c] + min(w * rw, nr), rows = max(0, min(rw, nr - w * rw));
+  int k[CELL_LANE_ROWS], k1[CELL_LANE_ROWS];
+  bool ones = true;
+#pragma unroll
+  for (int r = 0; r < CELL_LANE_ROWS; r++) {
+    const int i = lane + 64 * r;
+    k[r] = k1[r] = 0;
+    if (i < rows) {
+      k[r] = m.rp[r0 + i];
+      k1[r] = m.rp[r0 + i + 1];
+      if (!FILL) ones = ones && m.d[r0 + i] == (T)1;
+    }
+  }
+  int e = FILL ? m.rp[r0] : 0, s = FILL ? sbase[list] : 0;
+  for (int p = 0; p < P; p++) {
+    const int start = lo + p * PW;
+    int cnt[CELL_LANE_ROWS], most = 0;
+#pragma unroll
+    for (int r = 0; r < CELL_LANE_ROWS; r++) {
+      int j = k[r];
+      while (j < k1[r] && m.col[j] < start + PW) j++;
+      cnt[r] = j - k[r];
+      most = max(most, cnt[r]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+    for (int j = 0; j < most; j++) {
+      int pre = 0;
+#pragma unroll
+      for (int r = 0; r < CELL_LANE_ROWS; r++) {
+        const unsigned long long mask = __ballot(cnt[r] > j);
+        if (FILL && cnt[r] > j) {
+          const int at = e + pre + lanes_below(mask);
+          val[at] = m.val[k[r] + j];
+          ix[at] = ((uint32_t)(lane + 64 * r) << CELL_COL_BITS) | (uint32_t)(m.col[k[r] + j] - start);
+        }
+        pre += __popcll(mask);
+      }
+      const int steps = (pre + 63) / 64;
+      if (FILL && lane < steps)
+        step[s + lane] = (p << CELL_STEP_BITS) | (lane == 0 ? 1 << (CELL_STEP_BITS - 1) : 0) | min(64, pre - 64 * lane);
+      e += pre;
+      s += steps;
+    }
+#pragma unroll
+    for (int r = 0; r < CELL_LANE_ROWS; r++) k[r] += cnt[r];
+  }
+  if (FILL && lane == 0 && list == tl.ntile * CELL_WAVES - 1) {  // read past the last list, not used
+    val[e] = (T)0;
+    ix[e] = 0u;
+  }
+  if (!FILL) {
+    if (lane == 0) nstep[list] = s;
+    if (__ballot(!ones) != 0 && lane == 0) unit[c] = 0;
+  }
+}
+// Tile records in the order of the blocks' lists, one thread per word.
+__global__ void k_cells_rec(Tiles tl, const int32_t* __restrict__ order, const int32_t* __restrict__ rp,
+                            const int32_t* __restrict__ sbase, const int32_t* __restrict__ unit,
+                            int32_t* __restrict__ rec) {
+  const int i = blockIdx.x * BS + threadIdx.x;
+  if (i >= tl.ntile * CR_WORDS) return;
+  const int c = order[i / CR_WORDS], f = i % CR_WORDS;
+  const int nr = tl.nrows[c], inst = tl.inst[c];
+  int v = 0;
+  switch (f) {
+    case CR_ROW0: v = tl.row0[c]; break;
+    case CR_NROWS: v = nr; break;
+    case CR_LO: v = tl.w0[c]; break;
+    case CR_COLS: v = tl.nw[c]; break;
+    case CR_INST: v = inst; break;
+    case CR_TILE: v = c; break;
+    case CR_T0: v = tl.inst_t0[inst]; break;
+    case CR_T1: v = tl.inst_t0[inst + 1]; break;
+    case CR_UNIT: v = unit[c]; break;
+    default:
+      if (f < CR_STEP) v = rp[tl.row0[c] + min((f - CR_ENTRY) * cell_wave_rows(nr), nr)];
+      else if (f <= CR_STEP + CELL_WAVES) v = sbase[c * CELL_WAVES + f - CR_STEP];
+  }
+  rec[i] = v;
+}
+template <typename T>
+hipError_t launch_cells_count(hipStream_t st, MatView<T> m, Tiles tl, int32_t* nstep, int32_t* unit) {
+  if (tl.ntile <= 0) return hipSuccess;
+  hipError_t e = launch_fill_u32(st, reinterpret_cast<uint32_t*>(unit), tl.ntile, 1u);
+  if (e != hipSuccess) return e;
+  const unsigned g = (unsigned)(tl.ntile * CELL_WAVES / (BS / 64));
+  k_cells_build<T, false><<<g, BS, 0, st>>>(m, tl, nullptr, nstep, unit, nullptr, nullptr, nullptr);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_cells_fill(hipStream_t st, MatView<T> m, Tiles tl, const int32_t* order, const int32_t* sbase,
+                             const int32_t* unit, int32_t* step, T* val, uint32_t* ix, int32_t* rec) {
+  if (tl.ntile <= 0) return hipSuccess;
+  const unsigned g = (unsigned)(tl.ntile * CELL_WAVES / (BS / 64));
+  k_cells_build<T, true><<<g, BS, 0, st>>>(m, tl, sbase, nullptr, nullptr, step, val, ix);
+  k_cells_rec<<<grid_for((int64_t)tl.ntile * CR_WORDS), BS, 0, st>>>(tl, order, m.rp, sbase, unit, rec);
+  return hipGetLastError();
+}
+
+constexpr int CELL_DEPTH = 8;  // steps of a wavefront in flight (divides 64)
+constexpr int CELL_NT = (CELL_WAVES + 2 * CELL_TEAM) * 64;  // threads of a block
+
+// Barrier that orders LDS accesses only: loads from global memory stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Waits for a loaded value on every path from here: a load that some path
+// leaves unused would otherwise be waited for, with all the loads after it,
+// wherever its register is written next.
+template <typename V>
+__device__ __forceinline__ void arrived(V v) {
+  asm volatile("" ::"v"(v));
+}
+
+// The steps of a wavefront's list in order: word s of the list, 64 of them at
+// a time in the lanes of one register, the next 64 on their way.
+struct CellSteps {
+  int cur, nxt;
+  const int32_t* p;
+  int n;
+  __device__ __forceinline__ int at(int s, int lane) const { return p[min(s + lane, max(n - 1, 0))]; }
+  __device__ __forceinline__ void begin(const int32_t* step, int s0, int s1, int lane) {
+    n = s1 - s0;
+    p = step + (n > 0 ? s0 : 0);
+    cur = at(0, lane);
+    nxt = at(64, lane);
+  }
+  // before words s .. s + CELL_DEPTH - 1 (s a multiple of CELL_DEPTH)
+  __device__ __forceinline__ void move(int s, int lane) {
+    if (s % 64 == 0) {
+      cur = nxt;
+      nxt = at(s + 64, lane);
+    }
+  }
+  __device__ __forceinline__ int word(int s) const { return s < n ? __builtin_amdgcn_readlane(cur, s % 64) : 0; }
+};
+
+// One step: its word (in a scalar register) and each lane's entry.  Loaded
+// without branches (lanes past the step's entries read its last one), so that
+// the loads of the steps after it stay in flight while it is used.
+template <typename T>
+struct CellStep {
+  int w;
+  T v;
+  uint32_t ix;
+  __device__ __forceinline__ int count() const { return w & ((1 << (CELL_STEP_BITS - 1)) - 1); }
+  __device__ __forceinline__ void load(const Cells<T>& cl, int word, int& e, int lane) {
+    w = word;
+    const unsigned k = (unsigned)min(lane, max(count() - 1, 0));
+    v = __builtin_nontemporal_load(cl.val + e + k);
+    ix = __builtin_nontemporal_load(cl.ix + e + k);
+    e += count();
+  }
+};
+
+// Adds N steps of one panel to the sums; the rows of all of them differ.
+template <typename T, int N>
+__device__ __forceinline__ void cell_add(const CellStep<T>* b, const T* xs, T* yw, int lane) {
+  T xv[N], yv[N], *y[N];
+#pragma unroll
+  for (int u = 0; u < N; u++) {
+    y[u] = yw + (b[u].ix >> CELL_COL_BITS);
+    xv[u] = xs[b[u].ix & ((1u << CELL_COL_BITS) - 1u)];
+    yv[u] = *y[u];
+  }
+#pragma unroll
+  for (int u = 0; u < N; u++) {
+    const T f = yv[u] + b[u].v * xv[u];
+    if (lane < b[u].count()) *y[u] = f;
+  }
+  // the next rank may read a sum that another lane wrote
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// The tiles of one block.  Job:
+//   pre(inst, t0, t1, lane)   loads what live() needs (kept until the tile starts)
+//   live(rec...)              whether the tile is swept (the same in every wavefront)
+//   row<UNIT>(row, d, a, xo, acc)  one row: d its diagonal (1 if UNIT), a = job.vec()[row],
+//                             xo = x[row], acc its sum
+//   out(tile, v)              the tile's NV reduced values (bit i of MAXMASK: max, else sum)
+// The staging wavefronts are separate from the adding ones so that waiting for
+// a panel does not wait for the entries loaded after it (loads complete in
+// order within a wavefront); a team loads its next panel as soon as its last one
+// is in LDS, two panels ahead.
+template <typename T, typename Job>
+__device__ __forceinline__ void cell_tiles(const Cells<T>& cl, const T* __restrict__ x, Job& job) {
+  extern __shared__ unsigned char smem_raw[];
+  T* ys = reinterpret_cast<T*>(smem_raw);
+  T* xs = ys + CELL_ROWS;
+  __shared__ double red[CELL_WAVES][Job::NV];
+  constexpr int PW = cell_panel<T>();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int i0 = cl.blk[blockIdx.x], i1 = cl.blk[blockIdx.x + 1];
+  if (i0 >= i1) return;
+  int rec = cl.rec[(size_t)i0 * CR_WORDS + (lane & (CR_WORDS - 1))];
+  typename Job::Pre pre = job.pre(__builtin_amdgcn_readlane(rec, CR_INST), __builtin_amdgcn_readlane(rec, CR_T0),
+                                  __builtin_amdgcn_readlane(rec, CR_T1), lane);
+  bool busy = false;  // a tile of this block is or was in the LDS
+  if (wave >= CELL_WAVES) {
+    constexpr int NT = CELL_TEAM * 64, V = 16 / sizeof(T), PV = PW / V;
+    static_assert(PV == CELL_REGS * NT, "a team's registers hold one panel");
+    const int team = wave >= CELL_WAVES + CELL_TEAM ? 1 : 0;
+    const int t = threadIdx.x - (CELL_WAVES + team * CELL_TEAM) * 64;
+    f32x4* xd = reinterpret_cast<f32x4*>(xs) + t;
+    f32x4 pan[CELL_REGS];
+    // the team's panel that starts v vectors into the block of cv vectors at
+    // row lo (none there: one line, not used)
+    auto fetch = [&](int lo, int cv, int v) {
+      const int v1 = v < cv ? v : 0;
+      const f32x4* __restrict__ xb = reinterpret_cast<const f32x4*>(x + lo) + v1;  // PAD rows: 16-byte aligned
+      const unsigned last = (unsigned)(v < cv ? cv - 1 - v : 0);
+#pragma unroll
+      for (int j = 0; j < CELL_REGS; j++) pan[j] = xb[min((unsigned)(t + j * NT), last)];
+    };
+    fetch(__builtin_amdgcn_readlane(rec, CR_LO), __builtin_amdgcn_readlane(rec, CR_COLS) / V, team * PV);
+    int done = -1;  // tile whose values wait in red
+    for (int i = i0; i < i1; i++) {
+      const int next = cl.rec[(size_t)min(i + 1, i1 - 1) * CR_WORDS + (lane & (CR_WORDS - 1))];
+      const int lo = __builtin_amdgcn_readlane(rec, CR_LO), cv = __builtin_amdgcn_readlane(rec, CR_COLS) / V;
+      job.wait(pre);
+      if (job.live(rec, pre)) {
+        if (busy) lds_barrier();  // the panel and the rows of the tile before
+        busy = true;
+        if (threadIdx.x == CELL_WAVES * 64 && done >= 0) job.out(done, red);
+        done = __builtin_amdgcn_readlane(rec, CR_TILE);
+        if (team == 1) lds_barrier();  // the first panel is the other team's
+        for (int v0 = team * PV; v0 < cv; v0 += 2 * PV) {
+          if (v0 > 0) lds_barrier();  // every wavefront is done with the panel before
+          // (a last panel's registers past the block hold its last line)
+#pragma unroll
+          for (int j = 0; j < CELL_REGS; j++) xd[j * NT] = pan[j];
+          lds_barrier();
+          fetch(lo, cv, v0 + 2 * PV);  // behind the barrier: the issue of the loads takes time
+          if (v0 + PV < cv) {  // the other team's panel
+            lds_barrier();
+            lds_barrier();
+          }
+        }
+      }
+      fetch(__builtin_amdgcn_readlane(next, CR_LO), __builtin_amdgcn_readlane(next, CR_COLS) / V, team * PV);
+      rec = next;
+      pre = job.pre(__builtin_amdgcn_readlane(rec, CR_INST), __builtin_amdgcn_readlane(rec, CR_T0),
+                    __builtin_amdgcn_readlane(rec, CR_T1), lane);
+    }
+    if (busy) lds_barrier();
+    if (done >= 0 && threadIdx.x == CELL_WAVES * 64) job.out(done, red);
+    return;
+  }
+  constexpr int DEPTH = CELL_DEPTH;
+  CellStep<T> b[DEPTH];
+  CellSteps steps;
+  int e = 0;
+  const int first = rec;
+  for (int i = i0 - 1; i < i1; i++) {  // (i0 - 1: only the first tile's loads)
+    const int next = i < i0 ? first : cl.rec[(size_t)min(i + 1, i1 - 1) * CR_WORDS + (lane & (CR_WORDS - 1))];
+    job.wait(pre);
+    const bool live = i >= i0 && job.live(rec, pre);
+    const int row0 = __builtin_amdgcn_readlane(rec, CR_ROW0), nr = __builtin_amdgcn_readlane(rec, CR_NROWS);
+    const int cols = __builtin_amdgcn_readlane(rec, CR_COLS);
+    const bool unit = __builtin_amdgcn_readlane(rec, CR_UNIT) != 0;
+    const int rw = cell_wave_rows(nr);
+    T* yw = ys + wave * (CELL_ROWS / CELL_WAVES);
+    if (live) {
+      for (int k = lane; k < rw; k += 64) yw[k] = (T)0;
+      if (busy) lds_barrier();  // the panel of the tile before
+      busy = true;
+      lds_barrier();
+      int p = 0;
+      auto panel = [&](int q) {
+        for (; p < q; p++) {
+          lds_barrier();
+          lds_barrier();
+        }
+      };
+      // DEPTH steps at a time, those past the list's end empty: leaving the
+      // loop only here keeps the number of loads in flight known at every wait
+      for (int s = 0; s < steps.n; s += DEPTH) {
+        steps.move(s + DEPTH, lane);
+#pragma unroll
+        for (int r = 0; r < DEPTH; r += 2) {
+          if (b[r].w != 0) {
+            panel(b[r].w >> CELL_STEP_BITS);
+            // two steps of one rank at once
+            if ((b[r + 1].w & (1 << (CELL_STEP_BITS - 1))) == 0) {
+              cell_add<T, 2>(b + r, xs, yw, lane);
+            } else {
+              cell_add<T, 1>(b + r, xs, yw, lane);
+              panel(b[r + 1].w >> CELL_STEP_BITS);
+              cell_add<T, 1>(b + r + 1, xs, yw, lane);
+            }
+          }
+          b[r].load(cl, steps.word(s + DEPTH + r), e, lane);
+          b[r + 1].load(cl, steps.word(s + DEPTH + r + 1), e, lane);
+        }
+      }
+      panel((cols - 1) / PW);  // panels of the other wavefronts
+    }
+    // the wavefront's rows, G x 64 at a time; the next tile's first entries
+    // are loaded behind the first group's vectors, before those are used
+    constexpr int G = 4;
+    const int k0 = wave * rw, k1 = live ? min(nr, wave * rw + rw) : 0;
+    const T* __restrict__ vec = job.vec();
+    const T* __restrict__ vb = vec + row0;
+    const T* __restrict__ xb = x + row0;
+    const T* __restrict__ db = cl.d + row0;
+    job.begin();
+    int k = k0;
+    do {
+      T av[G], xo[G], dv[G];
+#pragma unroll
+      for (int g = 0; g < G; g++) {
+        const unsigned j = (unsigned)min(k + 64 * g + lane, nr - 1);
+        av[g] = vec ? vb[j] : (T)0;
+        xo[g] = xb[j];
+        dv[g] = unit ? (T)1 : db[j];
+      }
+      if (k == k0) {
+        pre = job.pre(__builtin_amdgcn_readlane(next, CR_INST), __builtin_amdgcn_readlane(next, CR_T0),
+                      __builtin_amdgcn_readlane(next, CR_T1), lane);
+        e = __builtin_amdgcn_readlane(next, CR_ENTRY + wave);
+        steps.begin(cl.step, __builtin_amdgcn_readlane(next, CR_STEP + wave),
+                    __builtin_amdgcn_readlane(next, CR_STEP + wave + 1), lane);
+#pragma unroll
+        for (int r = 0; r < DEPTH; r++) b[r].load(cl, steps.word(r), e, lane);
+      }
+#pragma unroll
+      for (int g = 0; g < G; g++) {
+        arrived(av[g]);
+        arrived(xo[g]);
+        arrived(dv[g]);
+      }
+#pragma unroll
+      for (int g = 0; g < G; g++) {
+        const int j = k + 64 * g + lane;
+        if (j < k1) {
+          if (unit) job.template row<true>(row0 + j, (T)1, av[g], xo[g], yw[j - k0]);
+          else job.template row<false>(row0 + j, dv[g], av[g], xo[g], yw[j - k0]);
+        }
+      }
+      k += 64 * G;
+    } while (k < k1);
+    if (live) {
+#pragma unroll
+      for (int v = 0; v < Job::NV; v++) {
+        double a = job.v[v];
+        const bool ismax = (Job::MAXMASK >> v) & 1u;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+          const double w = __shfl_xor(a, o, 64);
+          a = ismax ? mx(a, w) : a + w;
+        }
+        if (lane == 0) red[wave][v] = a;
+      }
+    }
+    rec = next;
+  }
+  if (busy) lds_barrier();
+}
+
+// Values of a tile from its wavefronts', in order.
+template <int NV, unsigned MAXMASK>
+__device__ __forceinline__ void cell_out(const double (&red)[CELL_WAVES][NV], double* __restrict__ part, int tile) {
+#pragma unroll
+  for (int v = 0; v < NV; v++) {
+    double a = red[0][v];
+#pragma unroll
+    for (int w = 1; w < CELL_WAVES; w++) a = ((MAXMASK >> v) & 1u) ? mx(a, red[w][v]) : a + red[w][v];
+    part[(size_t)tile * NV + v] = a;
+  }
+}
+
+template <typename T>
+struct JacobiCells {
+  static constexpr int NV = 1;
+  static constexpr unsigned MAXMASK = 1u;
+  struct Pre {
+    double pv, th;
+    int32_t st;
+  };
+  const T* __restrict__ rhs;
+  T* __restrict__ xn;
+  const double* __restrict__ pprev;
+  double* __restrict__ pcur;
+  const double* __restrict__ thr;
+  int32_t* status;
+  int64_t* iters;
+  double* meas;
+  int32_t* ndone;
+  int64_t s, max_iter;
+  int strict, weighted;
+  double v[1];
+
+  __device__ __forceinline__ const T* vec() const { return rhs; }
+  __device__ __forceinline__ Pre pre(int inst, int t0, int t1, int lane) const {
+    Pre p{0.0, 0.0, status[inst]};
+    if (s > 0) {
+      p.pv = pprev[min(t0 + lane, t1 - 1)];
+      p.th = thr[inst];
+    }
+    return p;
+  }
+  __device__ __forceinline__ void wait(const Pre& p) const {
+    arrived(p.pv);
+    arrived(p.th);
+    arrived(p.st);
+  }
+  // the decision on sweep s - 1, as jacobi_decide takes it
+  __device__ __forceinline__ bool live(int rec, const Pre& p) const {
+    if (__builtin_amdgcn_readfirstlane(p.st) != ST_RUN) return false;
+    if (s == 0) return true;
+    const int lane = threadIdx.x & 63;
+    const int t0 = __builtin_amdgcn_readlane(rec, CR_T0), t1 = __builtin_amdgcn_readlane(rec, CR_T1);
+    double m = p.pv;
+    for (int t = t0 + 64 + lane; t < t1; t += 64) m = mx(m, pprev[t]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = mx(m, __shfl_xor(m, o, 64));
+    int32_t st = ST_RUN;
+    if (!finite(m)) st = ST_NONFINITE;
+    else if (strict ? (m < p.th) : (m <= p.th)) st = ST_CONVERGED;
+    else if (s >= max_iter) st = ST_MAXITER;
+    st = __builtin_amdgcn_readfirstlane(st);
+    if (threadIdx.x == 0 && __builtin_amdgcn_readlane(rec, CR_TILE) == t0) {
+      const int inst = __builtin_amdgcn_readlane(rec, CR_INST);
+      meas[inst] = m;  // latest measure, also while running (stagnation watch)
+      if (st != ST_RUN) {
+        status[inst] = st;
+        iters[inst] = s;
+        atomicAdd(ndone, 1);
+      }
+    }
+    return st == ST_RUN;
+  }
+  __device__ __forceinline__ void begin() { v[0] = 0.0; }
+  template <bool UNIT>
+  __device__ __forceinline__ void row(int row, T d, T b, T xo, T acc) {
+    const T nv = UNIT ? b + acc : (b + acc) / d;
+    const double dl = fabs((double)nv - (double)xo);
+    xn[row] = nv;
+    v[0] = mx(v[0], !UNIT && weighted ? (double)d * dl : dl);
+  }
+  __device__ __forceinline__ void out(int tile, const double (&red)[CELL_WAVES][1]) const {
+    cell_out<1, 1u>(red, pcur, tile);
+  }
+};
+
+template <typename T>
+__global__ __launch_bounds__(CELL_NT) void k_jacobi_cells(Cells<T> cl, const T* __restrict__ rhs,
+                                                          const T* __restrict__ x, T* __restrict__ xn, Tiles tl,
+                                                          int64_t s_rel, const double* __restrict__ pprev,
+                                                          double* __restrict__ pcur, int32_t* status, int64_t* iters,
+                                                          double* meas, const double* __restrict__ thr, int strict,
+                                                          int64_t max_iter, int32_t* ndone, int weighted) {
+  JacobiCells<T> job{rhs, xn, pprev, pcur, thr, status, iters, meas, ndone,
+                     s_rel + (tl.sbase ? *tl.sbase : 0), max_iter, strict, weighted, {0.0}};
+  cell_tiles<T>(cl, x, job);
+}
+
+template <typename T>
+static size_t cells_lds() {
+  return (size_t)(CELL_ROWS + cell_panel<T>()) * sizeof(T);
+}
+template <typename T>
+hipError_t launch_jacobi_cells(hipStream_t st, Cells<T> cl, const T* rhs, const T* x, T* xn, Tiles tl, int64_t s,
+                               const double* pprev, double* pcur, int32_t* status, int64_t* iters, double* meas,
+                               const double* thr, int strict, int64_t max_iter, int32_t* ndone, int weighted) {
+  static size_t conf = 0;
+  hipError_t e = set_lds(k_jacobi_cells<T>, cells_lds<T>(), conf);
+  if (e != hipSuccess) return e;
+  k_jacobi_cells<T><<<(unsigned)cl.nblk, CELL_NT, cells_lds<T>(), st>>>(cl, rhs, x, xn, tl, s, pprev, pcur, status,
+                                                                       iters, meas, thr, strict, max_iter, ndone,
+                                                                       weighted);
+  return hipGetLastError();
+}
+
+// y = d u - A_off u and its dot products, or the residual (modes as k_spmv_sliced).
+template <typename T, int MODE>
+struct SpmvCells {
+  static constexpr int NV = MODE == 1 ? 2 : 1;
+  static constexpr unsigned MAXMASK = MODE == 2 ? 1u : 0u;
+  struct Pre {
+    int32_t st;
+  };
+  const T* __restrict__ qv;
+  T* __restrict__ y;
+  const int32_t* __restrict__ status;
+  double* __restrict__ part;
+  double v[NV];
+
+  __device__ __forceinline__ const T* vec() const { return MODE == 1 ? nullptr : qv; }
+  __device__ __forceinline__ Pre pre(int inst, int, int, int) const { return Pre{status[inst]}; }
+  __device__ __forceinline__ void wait(const Pre& p) const { arrived(p.st); }
+  __device__ __forceinline__ bool live(int, const Pre& p) const {
+    return __builtin_amdgcn_readfirstlane(p.st) == ST_RUN;
+  }
+  __device__ __forceinline__ void begin() {
+#pragma unroll
+    for (int i = 0; i < NV; i++) v[i] = 0.0;
+  }
+  template <bool UNIT>
+  __device__ __forceinline__ void row(int row, T d, T q, T ui, T acc) {
+    const T yi = UNIT ? ui - acc : d * ui - acc;
+    if (MODE == 2) {
+      const T ri = q - yi;
+      y[row] = ri;
+      v[0] = mx(v[0], fabs((double)ri));
+    } else if (MODE == 0) {
+      y[row] = yi;
+      v[0] += (double)q * (double)yi;
+    } else {
+      y[row] = yi;
+      v[0] += (double)yi * (double)ui;
+      v[NV - 1] += (double)yi * (double)yi;
+    }
+  }
+  __device__ __forceinline__ void out(int tile, const double (&red)[CELL_WAVES][NV]) const {
+    cell_out<NV, MAXMASK>(red, part, tile);
+  }
+};
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(CELL_NT) void k_spmv_cells(Cells<T> cl, const T* __restrict__ u, T* __restrict__ y,
+                                                        const T* __restrict__ qv, const int32_t* __restrict__ status,
+                                                        double* __restrict__ part) {
+  SpmvCells<T, MODE> job{qv, y, status, part, {}};
+  cell_tiles<T>(cl, u, job);
+}
+template <typename T, int MODE>
+static hipError_t spmv_cells_M(hipStream_t st, Cells<T> cl, const T* u, T* y, const T* qv, const int32_t* status,
+                               double* part) {
+  static size_t conf = 0;
+  hipError_t e = set_lds(k_spmv_cells<T, MODE>, cells_lds<T>(), conf);
+  if (e != hipSuccess) return e;
+  k_spmv_cells<T, MODE><<<(unsigned)cl.nblk, CELL_NT, cells_lds<T>(), st>>>(cl, u, y, qv, status, part);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_spmv_cells(hipStream_t st, int mode, Cells<T> cl, const T* u, T* y, const T* qv,
+                             const int32_t* status, double* part) {
+  if (mode == 2) return spmv_cells_M<T, 2>(st, cl, u, y, qv, status, part);
+  return mode ? spmv_cells_M<T, 1>(st, cl, u, y, qv, status, part)
+              : spmv_cells_M<T, 0>(st, cl, u, y, qv, status, part);
+}
+#define RP_CELLS_INST(T)                                                                                              \
+  template hipError_t launch_cells_count<T>(hipStream_t, MatView<T>, Tiles, int32_t*, int32_t*);                      \
+  template hipError_t launch_cells_fill<T>(hipStream_t, MatView<T>, Tiles, const int32_t*, const int32_t*,            \
+                                           const int32_t*, int32_t*, T*, uint32_t*, int32_t*);                        \
+  template hipError_t launch_jacobi_cells<T>(hipStream_t, Cells<T>, const T*, const T*, T*, Tiles, int64_t,           \
+                                             const double*, double*, int32_t*, int64_t*, double*, const double*, int, \
+                                             int64_t, int32_t*, int);                                                 \
+  template hipError_t launch_spmv_cells<T>(hipStream_t, int, Cells<T>, const T*, T*, const T*, const int32_t*,        \
+                                           double*);
+RP_CELLS_INST(double)
+RP_CELLS_INST(float)
+#undef RP_CELLS_INST
+
+// ============================================================================
 // BiCGStab (Section 3.2), one instance-batched step per kernel; all scalars
 // (rho = q.r, alpha, omega, beta) are FP64 device arrays, one per instance.
 // ============================================================================
