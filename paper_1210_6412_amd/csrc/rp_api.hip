@@ -616,12 +616,12 @@ void ensure_transpose(rp_context* ctx, rp_system* s) {
   HIPCHK(ctx, transpose_temp_bytes(np, s->z, &tb));
   dalloc(ctx, temp, tb);
   dalloc(ctx, s->tr.rp, (size_t)np + 1);
-  dalloc(ctx, s->tr.col, (size_t)s->z);
-  dalloc(ctx, s->tr.v64, (size_t)s->z);
-  dalloc(ctx, s->tr.v32, (size_t)s->z);
+  dalloc(ctx, s->tr.col, (size_t)s->z + 1);
+  dalloc(ctx, s->tr.v64, (size_t)s->z + 1);
+  dalloc(ctx, s->tr.v32, (size_t)s->z + 1);
   HIPCHK(ctx, launch_transpose(ctx->stream, np, s->z, s->fwd.rp.p, s->fwd.col.p, s->fwd.v64.p, s->tr.rp.p,
                                s->tr.col.p, s->tr.v64.p, s->tr.v32.p, erow.p, idx.p, key.p, perm.p, temp.p, tb));
-  dalloc(ctx, s->tr.c16, (size_t)s->z);
+  dalloc(ctx, s->tr.c16, (size_t)s->z + 1);
   HIPCHK(ctx, launch_col16(ctx->stream, s->ch, s->roff.p, s->tr.rp.p, s->tr.col.p, s->tr.c16.p));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   s->have_tr = true;
@@ -2501,9 +2501,9 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
     s->z_h.resize(K);
     for (int k = 0; k < K; k++) s->z_h[k] = ath[k + 1] - ath[k];
   }
-  dalloc(ctx, s->fwd.col, (size_t)z);
-  dalloc(ctx, s->fwd.v64, (size_t)z);
-  dalloc(ctx, s->fwd.v32, (size_t)z);
+  dalloc(ctx, s->fwd.col, (size_t)z + 1);
+  dalloc(ctx, s->fwd.v64, (size_t)z + 1);
+  dalloc(ctx, s->fwd.v32, (size_t)z + 1);
   HIPCHK(ctx, launch_fill_rows(st, np, s->row_state.p, chain->row_ptr, chain->col, chain->val, s->cls.p, s->map.p,
                                s->fwd.rp.p, s->fwd.col.p, s->fwd.v64.p, s->fwd.v32.p, s->general ? 1 : 0));
 
@@ -2543,7 +2543,7 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   s->chunk_inst_h = cinst;
   s->chunk_c0_h = c0;
   s->ch = Chunks{s->c_row0.p, s->c_nrows.p, s->c_inst.p, s->c_inst0.p, nchunk, K};
-  dalloc(ctx, s->fwd.c16, (size_t)z);
+  dalloc(ctx, s->fwd.c16, (size_t)z + 1);
   HIPCHK(ctx, launch_col16(st, s->ch, s->roff.p, s->fwd.rp.p, s->fwd.col.p, s->fwd.c16.p));
 
   // -- LDS tiles for FP64 and FP32 windows; instances too large for a

@@ -1101,6 +1101,31 @@ __device__ __forceinline__ void stage_window(T* __restrict__ xs, const T* __rest
 // the blocks per CU of the FP32 sweep; it measured slower.)
 constexpr int TU = 2, TJ = 4;
 constexpr int kNoEntry = INT_MIN;
+// With one wavefront per row (rows of hundreds of entries) a batch holds up to
+// J x 64 entries of a row, two neighbours per lane and load, and the first row's
+// loads are issued before the x window is staged.  8,192 states with 820 entries
+// per row, us per sweep: FP64 25.3 -> 18.6, FP32 22.3 -> 15.9 (four entries per
+// lane, one per load, after the window, before); a plain sum over as many bytes
+// (67 MB, out of the last-level cache) takes 18.6, so the cache's rate and the
+// launch bound it now.  Two rows per wavefront at once were slower (20.9: 128
+// VGPRs and spills), and so were 32 lanes per row (25.4).  With shorter rows the
+// window's loads, which wait for those before them, came later instead (two and
+// four lanes per row: up to 60% slower), so they keep the order.
+template <typename T, int L>
+struct TileShape {
+  static constexpr int U = TU, J = TJ;
+  static constexpr bool EARLY = false;
+};
+template <>
+struct TileShape<double, 64> {
+  static constexpr int U = 1, J = 16;
+  static constexpr bool EARLY = true;
+};
+template <>
+struct TileShape<float, 64> {
+  static constexpr int U = 1, J = 16;
+  static constexpr bool EARLY = true;
+};
 
 // Tile handled by this block.  Workgroups are dispatched to the 8 XCDs in
 // turn (block b runs on XCD b mod 8); numbering the tiles so that each XCD
@@ -1136,12 +1161,12 @@ __device__ __forceinline__ int colrel(const MatView<T>& m, int k, int w0) {
   return m.col[k] - w0;
 }
 
-template <typename T, int L>
+template <typename T, int L, int U = TU, int J = TJ>
 struct RowBatch {
-  int k0[TU], k1[TU];
-  T bi[TU], di[TU];
-  int cc[TU][TJ];
-  T vv[TU][TJ];
+  int k0[U], k1[U];
+  T bi[U], di[U];
+  int cc[U][J];
+  T vv[U][J];
 
   // rows base + u*RPP + g of the tile; rhs may be null (not needed)
   template <int KIND>
@@ -1149,7 +1174,7 @@ struct RowBatch {
                                        int lane, int w0) {
     constexpr int RPP = TNT / L;
 #pragma unroll
-    for (int u = 0; u < TU; u++) {
+    for (int u = 0; u < U; u++) {
       const int i = base + u * RPP + g;
       if (i < nr) {
         k0[u] = m.rp[r0 + i];
@@ -1161,9 +1186,9 @@ struct RowBatch {
       }
     }
 #pragma unroll
-    for (int u = 0; u < TU; u++)
+    for (int u = 0; u < U; u++)
 #pragma unroll
-      for (int j = 0; j < TJ; j++) {
+      for (int j = 0; j < J; j++) {
         const int k = k0[u] + lane + j * L;
         if (k < k1[u]) { cc[u][j] = colrel<KIND>(m, k, w0); vv[u][j] = m.val[k]; }
         else { cc[u][j] = kNoEntry; vv[u][j] = 0; }
@@ -1176,29 +1201,119 @@ struct RowBatch {
                                    int u, int lane, int w0) const {
     T acc = 0;
 #pragma unroll
-    for (int j = 0; j < TJ; j++)
+    for (int j = 0; j < J; j++)
       if (cc[u][j] != kNoEntry) acc += vv[u][j] * xget<KIND>(xs, xg, cc[u][j], nw, w0);
-    for (int k = k0[u] + lane + TJ * L; k < k1[u]; k += L) acc += m.val[k] * xget<KIND>(xs, xg, colrel<KIND>(m, k, w0), nw, w0);
+    for (int k = k0[u] + lane + J * L; k < k1[u]; k += L) acc += m.val[k] * xget<KIND>(xs, xg, colrel<KIND>(m, k, w0), nw, w0);
 #pragma unroll
     for (int o = L / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, L);
     return acc;
   }
 };
 
-// Jacobi rows of one tile: xn = (rhs + A_off x) / d; returns the tile's max of
-// the stopping measure (|dx|, or d |dx| when weighted).
-template <typename T, int L, int KIND>
-__device__ __forceinline__ double jacobi_rows(const MatView<T>& m, const T* __restrict__ rhs, const T* __restrict__ xs,
-                                              const T* __restrict__ x, T* __restrict__ xn, int r0, int nr, int w0,
-                                              int nw, int weighted) {
+// One wavefront per row: lane l takes the entries 2l, 2l+1 (+ 128 j) of the row,
+// both with one load (at any alignment).  A pair that reaches past the row's end
+// is moved back onto its last two entries (the arrays have spare elements for a
+// matrix of one entry); what is then not the lane's own counts as value 0 at
+// column 0 of the window.
+template <typename T, int U, int J>
+struct RowBatch<T, 64, U, J> {
+  using Val = T __attribute__((ext_vector_type(2), aligned(alignof(T))));
+  using Col = int __attribute__((ext_vector_type(2), aligned(4)));
+  using Col16 = uint16_t __attribute__((ext_vector_type(2), aligned(2)));
+  static constexpr int P = J / 2;
+  int k0[U], k1[U];
+  T bi[U], di[U];
+  Val vv[U][P];
+  Col cc[U][P];      // not used with 16-bit columns
+  Col16 hh[U][P];
+
+  __device__ __forceinline__ static int first(int k, int k1) { return max(min(k, k1 - 2), 0); }
+
+  template <int KIND>
+  __device__ __forceinline__ void load(const MatView<T>& m, const T* __restrict__ rhs, int r0, int nr, int base, int g,
+                                       int lane, int w0) {
+    const int row = __builtin_amdgcn_readfirstlane(r0 + base + g), end = r0 + nr;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int r = row + u * (TNT / 64);
+      k0[u] = r < end ? m.rp[r] : 0;
+      k1[u] = r < end ? m.rp[r + 1] : 0;
+      bi[u] = r < end && rhs ? rhs[r] : (T)0;
+      di[u] = r < end ? m.d[r] : (T)1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int j = 0; j < P; j++) {
+        vv[u][j] = (Val)(T)0;
+        cc[u][j] = (Col)0;
+        hh[u][j] = (Col16)(uint16_t)0;
+        if (k0[u] + j * 128 < k1[u]) read<KIND>(m, k0[u] + 2 * lane + j * 128, k1[u], vv[u][j], cc[u][j], hh[u][j]);
+      }
+  }
+  template <int KIND>
+  __device__ __forceinline__ static void read(const MatView<T>& m, int k, int k1, Val& v, Col& c, Col16& h) {
+    const int kk = first(k, k1);
+    v = *reinterpret_cast<const Val*>(m.val + kk);
+    if (KIND == WIN_WHOLE) h = *reinterpret_cast<const Col16*>(m.c16 + kk);
+    else c = *reinterpret_cast<const Col*>(m.col + kk);
+  }
+  // sum of the pair at k
+  template <int KIND>
+  __device__ __forceinline__ static T pair(const T* __restrict__ xs, const T* __restrict__ xg, int nw, int w0, int k,
+                                           int k1, Val v, Col c, Col16 h, T acc) {
+    const int c0 = KIND == WIN_WHOLE ? (int)h.x : c.x - w0, c1 = KIND == WIN_WHOLE ? (int)h.y : c.y - w0;
+    const bool in = k < k1, both = k + 1 < k1, back = k > 0 && !both;  // moved back: the lane's entry is the second
+    const T x0 = xget<KIND>(xs, xg, in ? (back ? c1 : c0) : 0, nw, w0), x1 = xget<KIND>(xs, xg, both ? c1 : 0, nw, w0);
+    acc += (in ? (back ? v.y : v.x) : (T)0) * x0;
+    acc += (both ? v.y : (T)0) * x1;
+    return acc;
+  }
+
+  // row sum of A_off times x for row u (valid in every lane)
+  template <int KIND>
+  __device__ __forceinline__ T sum(const MatView<T>& m, const T* __restrict__ xs, const T* __restrict__ xg, int nw,
+                                   int u, int lane, int w0) const {
+    T acc = 0;
+#pragma unroll
+    for (int j = 0; j < P; j++)
+      if (k0[u] + j * 128 < k1[u])
+        acc = pair<KIND>(xs, xg, nw, w0, k0[u] + 2 * lane + j * 128, k1[u], vv[u][j], cc[u][j], hh[u][j], acc);
+    for (int k = k0[u] + P * 128; k < k1[u]; k += 4 * 128) {
+      Val v[4];
+      Col c[4];
+      Col16 h[4];
+#pragma unroll
+      for (int j = 0; j < 4; j++) read<KIND>(m, k + 2 * lane + j * 128, k1[u], v[j], c[j], h[j]);
+#pragma unroll
+      for (int j = 0; j < 4; j++)
+        acc = pair<KIND>(xs, xg, nw, w0, k + 2 * lane + j * 128, k1[u], v[j], c[j], h[j], acc);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    return acc;
+  }
+};
+
+// Jacobi rows of one tile: xn = (rhs + A_off x) / d; mloc: the tile's max of
+// the stopping measure (|dx|, or d |dx| when weighted).  begin() runs before the
+// first rows' loads or (EARLY) between them and their use; nothing is written
+// when it returns false.
+template <typename T, int L, int KIND, typename Begin>
+__device__ __forceinline__ bool jacobi_rows(const MatView<T>& m, const T* __restrict__ rhs, const T* __restrict__ xs,
+                                            const T* __restrict__ x, T* __restrict__ xn, int r0, int nr, int w0,
+                                            int nw, int weighted, double& mloc, Begin begin) {
+  using S = TileShape<T, L>;
   const int g = threadIdx.x / L, lane = threadIdx.x % L;
   constexpr int RPP = TNT / L;
-  double mloc = 0.0;
-  for (int base = 0; base < nr; base += RPP * TU) {
-    RowBatch<T, L> rb;
+  mloc = 0.0;
+  if (!S::EARLY && !begin()) return false;
+  for (int base = 0; base < nr; base += RPP * S::U) {
+    RowBatch<T, L, S::U, S::J> rb;
     rb.template load<KIND>(m, rhs, r0, nr, base, g, lane, w0);
+    if (S::EARLY && base == 0 && !begin()) return false;
 #pragma unroll
-    for (int u = 0; u < TU; u++) {
+    for (int u = 0; u < S::U; u++) {
       const T acc = rb.template sum<KIND>(m, xs, x, nw, u, lane, w0);
       const int i = base + u * RPP + g;
       if (i < nr && lane == 0) {
@@ -1210,7 +1325,7 @@ __device__ __forceinline__ double jacobi_rows(const MatView<T>& m, const T* __re
       }
     }
   }
-  return mloc;
+  return true;
 }
 
 // Start of a tiled sweep s: copy the x window into LDS and take the decision
@@ -1252,12 +1367,16 @@ __global__ __launch_bounds__(TNT) void k_jacobi_tile(MatView<T> m, const T* __re
   const int r0 = tl.row0[c], nr = tl.nrows[c];
   if (status[inst] != ST_RUN) return;
   const int64_t s = s_rel + (tl.sbase ? *tl.sbase : 0);
-  if (!jacobi_begin<T>(xs, x, tl, c, inst, kind, w0, nw, s, pprev, status, iters, meas, thr, strict, max_iter, ndone))
-    return;
+  auto begin = [&]() {
+    return jacobi_begin<T>(xs, x, tl, c, inst, kind, w0, nw, s, pprev, status, iters, meas, thr, strict, max_iter,
+                           ndone);
+  };
   double mloc;
-  if (kind == WIN_WHOLE) mloc = jacobi_rows<T, L, WIN_WHOLE>(m, rhs, xs, x, xn, r0, nr, w0, nw, weighted);
-  else if (kind == WIN_BAND) mloc = jacobi_rows<T, L, WIN_BAND>(m, rhs, xs, x, xn, r0, nr, w0, nw, weighted);
-  else mloc = jacobi_rows<T, L, WIN_NONE>(m, rhs, xs, x, xn, r0, nr, w0, nw, weighted);
+  bool go;
+  if (kind == WIN_WHOLE) go = jacobi_rows<T, L, WIN_WHOLE>(m, rhs, xs, x, xn, r0, nr, w0, nw, weighted, mloc, begin);
+  else if (kind == WIN_BAND) go = jacobi_rows<T, L, WIN_BAND>(m, rhs, xs, x, xn, r0, nr, w0, nw, weighted, mloc, begin);
+  else go = jacobi_rows<T, L, WIN_NONE>(m, rhs, xs, x, xn, r0, nr, w0, nw, weighted, mloc, begin);
+  if (!go) return;
   double v[1] = {mloc};
   block_reduce<1, TNT>(v, 1u);
   if (threadIdx.x == 0) pcur[c] = v[0];
@@ -1903,18 +2022,22 @@ __global__ __launch_bounds__(TNT) void k_bicg_p_tile(const T* __restrict__ r, T*
 }
 
 // y = M u = d u - A_off u with u staged in LDS; partials: mode 0 q.y, mode 1 (y.u, y.y)
-// y = M u over one tile's rows; MODE 0 accumulates q.y, MODE 1 (y.u, y.y).
-template <typename T, int L, int MODE, int KIND>
+// y = M u over one tile's rows; MODE 0 accumulates q.y, MODE 1 (y.u, y.y);
+// begin() (staging u) as in jacobi_rows.
+template <typename T, int L, int MODE, int KIND, typename Begin>
 __device__ __forceinline__ void spmv_rows(const MatView<T>& m, const T* __restrict__ us, const T* __restrict__ u,
                                           T* __restrict__ y, const T* __restrict__ q, int r0, int nr, int w0, int nw,
-                                          double* a) {
+                                          double* a, Begin begin) {
+  using S = TileShape<T, L>;
   const int g = threadIdx.x / L, lane = threadIdx.x % L;
   constexpr int RPP = TNT / L;
-  for (int base = 0; base < nr; base += RPP * TU) {
-    RowBatch<T, L> rb;
+  if (!S::EARLY) begin();
+  for (int base = 0; base < nr; base += RPP * S::U) {
+    RowBatch<T, L, S::U, S::J> rb;
     rb.template load<KIND>(m, nullptr, r0, nr, base, g, lane, w0);
+    if (S::EARLY && base == 0) begin();
 #pragma unroll
-    for (int uu = 0; uu < TU; uu++) {
+    for (int uu = 0; uu < S::U; uu++) {
       const T acc = rb.template sum<KIND>(m, us, u, nw, uu, lane, w0);
       const int i = base + uu * RPP + g;
       if (i < nr && lane == 0) {
@@ -1942,14 +2065,15 @@ __global__ __launch_bounds__(TNT) void k_spmv_tile(MatView<T> m, const T* __rest
   const int c = tile_of(tl);
   if (status[tl.inst[c]] != ST_RUN) return;
   const int r0 = tl.row0[c], nr = tl.nrows[c], w0 = tl.w0[c], nw = tl.nw[c], kind = tl.kind[c];
-  if (kind != WIN_NONE) {
+  auto begin = [&]() {
+    if (kind == WIN_NONE) return;
     stage_window<T, TNT>(us, u, w0, nw);
     __syncthreads();
-  }
+  };
   double a[2] = {0.0, 0.0};
-  if (kind == WIN_WHOLE) spmv_rows<T, L, MODE, WIN_WHOLE>(m, us, u, y, q, r0, nr, w0, nw, a);
-  else if (kind == WIN_BAND) spmv_rows<T, L, MODE, WIN_BAND>(m, us, u, y, q, r0, nr, w0, nw, a);
-  else spmv_rows<T, L, MODE, WIN_NONE>(m, us, u, y, q, r0, nr, w0, nw, a);
+  if (kind == WIN_WHOLE) spmv_rows<T, L, MODE, WIN_WHOLE>(m, us, u, y, q, r0, nr, w0, nw, a, begin);
+  else if (kind == WIN_BAND) spmv_rows<T, L, MODE, WIN_BAND>(m, us, u, y, q, r0, nr, w0, nw, a, begin);
+  else spmv_rows<T, L, MODE, WIN_NONE>(m, us, u, y, q, r0, nr, w0, nw, a, begin);
   if (MODE == 0) {
     double b1[1] = {a[0]};
     block_reduce<1, TNT>(b1, 0u);
