@@ -220,7 +220,10 @@ struct SlicedSet {
   bool built = false, ok = false;
   DBuf<int32_t> t_s0, off, width, row, c32;
   DBuf<T> d, val;
-  DBuf<uint16_t> c16;
+  DBuf<uint16_t> c16, r16;
+  DBuf<SliceRec> rec;
+  DBuf<float> val32;
+  DBuf<int32_t> far, wide;
   // column panels
   DBuf<int32_t> npan, hoff, pent, pend;
   DBuf<uint8_t> cnt;
@@ -272,6 +275,7 @@ struct rp_system {
     DBuf<int32_t> row0, nrows, inst, inst0, w0, nw, kind, order;
     std::vector<uint8_t> whole_h;  // per instance: window kind WIN_WHOLE (16-bit columns)
     std::vector<int32_t> nrows_h;  // rows per tile
+    std::vector<int32_t> nw_h;     // window rows per tile
     std::vector<int32_t> kind_h;   // window kind per tile
     std::vector<int32_t> inst_h;   // instance per tile
     std::vector<int32_t> inst0_h;  // tiles of instance k: [inst0_h[k], inst0_h[k+1])
@@ -868,6 +872,7 @@ void build_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t w
   to_dev(ctx, ts.nw.p, tnw.data(), (size_t)nt);
   to_dev(ctx, ts.kind.p, tkind.data(), (size_t)nt);
   ts.nrows_h = tnr;
+  ts.nw_h = tnw;
   ts.kind_h = tkind;
   ts.inst_h = tinst;
   ts.inst0_h = tc0;
@@ -1237,6 +1242,10 @@ int32_t sort_window(const rp_system* s) {
   return mean < 5.0 ? 512 : 2048;
 }
 
+// Mean width of the slices below which they count as narrow: program graphs have
+// 3.2, chains with rows of 1 to 8 entries 4.7 (both measured at SliceShape).
+constexpr int kNarrowSlots = 4;
+
 // Sliced rows of the tile set for T and the forward or transposed matrix,
 // built once: a block per tile orders its rows and measures its slices, the
 // host lays the slices out (64-bit offsets, checked against int32), and a
@@ -1269,8 +1278,36 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   to_dev(ctx, ss.t_s0.p, t_s0.data(), (size_t)nt + 1);
   MatView<T> m = view<T>(s, tr);
   HIPCHK(ctx, launch_slice_order(st, m.rp, tl, ss.t_s0.p, sort_window(s), ss.row.p, ss.width.p));
-  std::vector<int32_t> width(nslice);
+  bool any_band = false;
+  for (int32_t t = 0; t < nt; t++) any_band = any_band || ts.kind_h[t] == WIN_BAND;
+  DBuf<int32_t> stile_d, nfar_d, far0_d, inexact;
+  dalloc(ctx, stile_d, (size_t)nslice);
+  to_dev(ctx, stile_d.p, stile.data(), (size_t)nslice);
+  dalloc(ctx, nfar_d, (size_t)nslice);
+  dalloc(ctx, far0_d, (size_t)nslice);
+  std::vector<int32_t> width(nslice), nfar(nslice, 0), far0(nslice, 0);
+  if (any_band) {
+    HIPCHK(ctx, launch_slice_far(st, m.rp, m.col, tl, stile_d.p, nslice, ss.row.p, nfar_d.p));
+    to_host(ctx, nfar.data(), nfar_d.p, (size_t)nslice);
+  }
   to_host(ctx, width.data(), ss.width.p, (size_t)nslice);
+  // 32-bit columns where 16 bits do not reach (see Sliced), and the places of
+  // the far entries' columns
+  std::vector<int32_t> wide(nt, 0);
+  int64_t nfars = 0;
+  for (int32_t t = 0; t < nt; t++) {
+    wide[t] = ts.kind_h[t] == WIN_NONE || (ts.kind_h[t] == WIN_BAND && ts.nw_h[t] > SLICE_FAR);
+    for (int32_t q = t_s0[t]; q < t_s0[t + 1]; q++) wide[t] = wide[t] || nfar[q] > SLICE;
+    for (int32_t q = t_s0[t]; q < t_s0[t + 1]; q++) {
+      if (wide[t]) nfar[q] = 0;
+      far0[q] = (int32_t)std::min<int64_t>(nfars, INT32_MAX);
+      nfars += nfar[q];
+    }
+    if (t_s0[t + 1] - t_s0[t] > (TNT / 64) * 64 || ts.nrows_h[t] >= 0xFFFF) {
+      set_err(ctx, "internal error: tile of %d rows on sliced rows", (int)ts.nrows_h[t]);
+      throw Fail{RP_ERR_HIP};
+    }
+  }
   // Column panels for the tiles of instances without a window (no band, too
   // large for the LDS), when the copies of the instance's iterate (once per
   // tile and sweep) stay below kPanelCopyShare of the sweep's bytes, the
@@ -1310,10 +1347,10 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
     total += (int64_t)width[i] * SLICE;
   }
   ss.built = true;
-  if (total > INT32_MAX || ncnt >= INT32_MAX) return false;
-  bool any_whole = false, any_other = false;
+  if (total + SLICE > INT32_MAX || ncnt >= INT32_MAX || nfars > INT32_MAX) return false;
+  bool any16 = false, any32 = false;
   for (int32_t t = 0; t < nt; t++)
-    if (npan[t] == 0) (ts.kind_h[t] == WIN_WHOLE ? any_whole : any_other) = true;
+    if (npan[t] == 0) (wide[t] ? any32 : any16) = true;
   // paneled slices: count bytes and entries per slice, then the entries laid
   // out after the regular slots
   const int32_t nps = (int32_t)pslice.size();
@@ -1348,30 +1385,61 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
       pstart[pslice[i]] = (int32_t)std::min<int64_t>(total + pent, INT32_MAX);
       pent += ent[i];
     }
-    if (total + pent > INT32_MAX) return false;
+    if (total + pent + PANEL_SLACK > INT32_MAX) return false;
     dalloc(ctx, ss.pent, (size_t)nslice);
     to_dev(ctx, ss.pent.p, pstart.data(), (size_t)nslice);
     to_dev(ctx, ss.width.p, width.data(), (size_t)nslice);  // paneled slices: no regular slots
   }
-  const int64_t nent = total + pent + (npaneled > 0 ? PANEL_SLACK : 0);
-  DBuf<int32_t> stile_d;
-  dalloc(ctx, stile_d, (size_t)nslice);
+  // slots: regular (nslot), of paneled slices, then zeros (SLICE, PANEL_SLACK)
+  const int64_t nent = total + pent + std::max(SLICE, PANEL_SLACK);
+  bool exact = false;
+  if constexpr (std::is_same<T, double>::value) {
+    if (npaneled == 0) {
+      dalloc(ctx, inexact, 1);
+      HIPCHK(ctx, launch_set_i32(st, inexact.p, 0));
+      HIPCHK(ctx, launch_inexact32(st, m.val, s->z, inexact.p));
+      exact = read_i32(ctx, inexact.p) == 0;
+    }
+  }
   dalloc(ctx, ss.off, (size_t)nslice);
-  dalloc(ctx, ss.d, (size_t)nslice * SLICE);
-  dalloc(ctx, ss.val, (size_t)std::max<int64_t>(nent, 1));
-  if (any_whole || npaneled > 0) dalloc(ctx, ss.c16, (size_t)std::max<int64_t>(nent, 1));
-  if (any_other) dalloc(ctx, ss.c32, (size_t)std::max<int64_t>(total, 1));
-  to_dev(ctx, stile_d.p, stile.data(), (size_t)nslice);
+  dalloc(ctx, ss.d, ((size_t)nslice + 1) * SLICE);
+  dalloc(ctx, ss.r16, ((size_t)nslice + 1) * SLICE);
+  dalloc(ctx, ss.rec, (size_t)nslice);
+  dalloc(ctx, ss.wide, (size_t)nt);
+  dalloc(ctx, ss.far, (size_t)std::max<int64_t>(nfars, 1));
+  if (exact) dalloc(ctx, ss.val32, (size_t)nent);
+  else dalloc(ctx, ss.val, (size_t)nent);
+  if (any16 || npaneled > 0) dalloc(ctx, ss.c16, (size_t)nent);
+  if (any32) dalloc(ctx, ss.c32, (size_t)nent);
   to_dev(ctx, ss.off.p, off.data(), (size_t)nslice);
-  HIPCHK(ctx, launch_slice_fill<T>(st, m, tl, stile_d.p, nslice, ss.off.p, ss.width.p, ss.row.p, ss.d.p, ss.val.p,
-                                   ss.c16.p, ss.c32.p));
+  to_dev(ctx, ss.wide.p, wide.data(), (size_t)nt);
+  to_dev(ctx, nfar_d.p, nfar.data(), (size_t)nslice);
+  to_dev(ctx, far0_d.p, far0.data(), (size_t)nslice);
+  ss.v = Sliced<T>{};
+  ss.v.t_s0 = ss.t_s0.p;
+  ss.v.off = ss.off.p;
+  ss.v.width = ss.width.p;
+  ss.v.row = ss.row.p;
+  ss.v.d = ss.d.p;
+  ss.v.val = ss.val.p;
+  ss.v.c16 = ss.c16.p;
+  ss.v.c32 = ss.c32.p;
+  ss.v.rec = ss.rec.p;
+  ss.v.r16 = ss.r16.p;
+  ss.v.val32 = ss.val32.p;
+  ss.v.far = ss.far.p;
+  ss.v.wide = ss.wide.p;
+  ss.v.nslice = nslice;
+  ss.v.nslot = (int32_t)(total + pent);
+  ss.v.narrow = total < (int64_t)kNarrowSlots * SLICE * nslice ? 1 : 0;
+  HIPCHK(ctx, launch_set_i32(st, ss.far.p, 0));  // read where a slice has none
+  HIPCHK(ctx, launch_slice_fill<T>(st, m, tl, stile_d.p, ss.v, far0_d.p, nfar_d.p));
   // Slices larger than the last-level cache are read with nontemporal loads:
   // they cannot stay cached from one sweep to the next anyway, and streaming
   // them keeps the vectors' lines (x', the right-hand side) cached.
-  const double slice_bytes = (double)total * (double)(sizeof(T) + (any_other ? 4 : 2)) +
+  const double slice_bytes = (double)total * (double)((exact ? sizeof(float) : sizeof(T)) + (any32 ? 4 : 2)) +
                              (double)pent * (double)(sizeof(T) + 2) + (double)ncnt;
-  const int32_t stream = slice_bytes > kStreamBytes ? 1 : 0;
-  ss.v = Sliced<T>{ss.t_s0.p, ss.off.p, ss.width.p, ss.row.p, ss.d.p, ss.val.p, ss.c16.p, ss.c32.p, stream};
+  ss.v.stream = slice_bytes > kStreamBytes ? 1 : 0;
   if (npaneled > 0) {
     HIPCHK(ctx, hipMemsetAsync(ss.val.p + (total + pent), 0, sizeof(T) * PANEL_SLACK, st));
     HIPCHK(ctx, hipMemsetAsync(ss.c16.p + (total + pent), 0, sizeof(uint16_t) * PANEL_SLACK, st));

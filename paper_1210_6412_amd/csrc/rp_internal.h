@@ -57,6 +57,7 @@ struct Tiles {
                            //         kernels count from *sbase (null: they are absolute)
 };
 constexpr size_t TILE_LDS_BYTES = 163840 - 512;  // dynamic LDS available to a tile block
+constexpr int TNT = 1024;  // threads per tile block
 
 // Sparse matrix M = diag(d) - A_off over the padded reduced rows.
 template <typename T>
@@ -74,18 +75,33 @@ struct MatView {
 // rows, one row per lane.  Entry j of lane l of slice s is at off[s] + SLICE*j
 // + l; rows shorter than the slice's width are padded with value 0 and
 // column 0.  Columns are relative to the tile's window start w0 (16-bit on
-// tiles whose window is the whole instance block, 32-bit on the others).
+// tiles whose window is the whole instance block, 32-bit on those without a
+// window).  On a tile with a band window they are 16-bit too: an entry outside
+// the window holds SLICE_FAR | i, i its number among the slice's entries
+// outside, whose columns are in `far`; a tile with a slice of more than SLICE
+// such entries (or a window of more than SLICE_FAR rows) has 32-bit columns.
 constexpr int SLICE = 64;
+constexpr int SLICE_FAR = 0x8000;
+// One record per slice for the sweeps, the records of a tile in the order in
+// which its wavefronts take them (slice i of the tile is taken by wavefront
+// i mod TNT/64; a wavefront's records are contiguous).
+struct SliceRec {
+  int32_t off;    // as Sliced::off
+  int32_t width;  // as Sliced::width; SLICE_UNIT is added when every diagonal entry is 1
+  int32_t far0;   // entries outside the window: far[far0, far0 + nfar)
+  int32_t nfar;
+};
+constexpr int32_t SLICE_UNIT = 1 << 30;
 template <typename T>
 struct Sliced {
   const int32_t* t_s0;   // [ntile+1] slices of tile t: [t_s0[t], t_s0[t+1])
   const int32_t* off;    // [nslice]  first slot of the slice
   const int32_t* width;  // [nslice]  entries per lane (longest row of the slice)
   const int32_t* row;    // [nslice*SLICE] row of each lane, -1 past the tile's last row
-  const T* d;            // [nslice*SLICE] diagonal of that row (1 where no row)
-  const T* val;          // [nslot]
-  const uint16_t* c16;   // [nslot] column - w0 (tiles with whole-block windows)
-  const int32_t* c32;    // [nslot] column - w0 (other tiles)
+  const T* d;            // [(nslice+1)*SLICE] diagonal of that row (1 where no row)
+  const T* val;          // [nslot+SLICE] null when val32 holds the values
+  const uint16_t* c16;   // [nslot+SLICE] column - w0 (16 bits, see above)
+  const int32_t* c32;    // [nslot+SLICE] column - w0 (32 bits)
   int32_t stream;        // 1: read val/columns with nontemporal loads (slices larger than the
                          //    last-level cache, so keeping them there only evicts the vectors)
   // Column panels.  A tile of an instance whose block is too large for one
@@ -107,6 +123,17 @@ struct Sliced {
   const int32_t* pend;   // [ntile] end (exclusive) of the instance block of a paneled tile
   int32_t pw;            // panel width (rows, a multiple of PAD)
   int32_t paneled;       // 1 when some tile is paneled
+  // For the sweeps.  Entries past a slice's width are read from the SLICE slots
+  // of zeros at nslot, and rows and diagonals of no slice from slice nslice (no
+  // rows, ones), so that no load is conditional.
+  const SliceRec* rec;   // [nslice]
+  const uint16_t* r16;   // [(nslice+1)*SLICE] row - first row of the tile (0xFFFF: no row)
+  const float* val32;    // FP64 values that are all exact in FP32 (coin flips), else null
+  const int32_t* far;    // columns outside the window of their slice (absolute rows)
+  const int32_t* wide;   // [ntile] 1: 32-bit columns
+  int32_t nslice;
+  int32_t nslot;
+  int32_t narrow;        // 1: slices of up to about four entries
 };
 // Most slices a wavefront of a paneled tile keeps sums for (rows of a paneled
 // tile <= PanelShape<T>::MAXS * 1024): a quarter of the 128 registers a lane
@@ -346,10 +373,16 @@ hipError_t launch_bicg_check(hipStream_t st, Tiles tl, int64_t j, const double* 
 // sliced rows: build (order + widths per tile, then the slices) and sweeps
 hipError_t launch_slice_order(hipStream_t st, const int32_t* rp, Tiles tl, const int32_t* t_s0, int32_t window,
                               int32_t* row, int32_t* width);
+// Band tiles (see Sliced): nfar[s] = entries of slice s outside its window.
+hipError_t launch_slice_far(hipStream_t st, const int32_t* rp, const int32_t* col, Tiles tl, const int32_t* stile,
+                            int32_t nslice, const int32_t* row, int32_t* nfar);
+// inexact <- 1 if one of the values [0, z) is not exact in FP32 (else unchanged)
+hipError_t launch_inexact32(hipStream_t st, const double* val, int64_t z, int32_t* inexact);
+// The arrays of `sl` (written through its pointers), from the matrix; off, width
+// and row of slice s, and the first and number of its far entries.
 template <typename T>
-hipError_t launch_slice_fill(hipStream_t st, MatView<T> m, Tiles tl, const int32_t* stile, int32_t nslice,
-                             const int32_t* off, const int32_t* width, const int32_t* row, T* d, T* val,
-                             uint16_t* c16, int32_t* c32);
+hipError_t launch_slice_fill(hipStream_t st, MatView<T> m, Tiles tl, const int32_t* stile, Sliced<T> sl,
+                             const int32_t* far0, const int32_t* nfar);
 // column panels: per paneled slice (pslice: slice index, ptile: its tile)
 // the count bytes (sl.cnt) and its number of entries; then the entries
 template <typename T>

@@ -16,6 +16,7 @@
 #include "rp_internal.h"
 
 #include <climits>
+#include <type_traits>
 
 #include <math.h>
 
@@ -1043,7 +1044,6 @@ hipError_t launch_fin_jacobi(hipStream_t st, Chunks ch, const double* partial, i
 // removes the separate finishing launch per sweep.
 // ============================================================================
 
-constexpr int TNT = 1024;  // threads per tile block
 
 // Decision on Jacobi sweep s-1 of an instance, taken by each wavefront on its
 // own: the instance's per-tile maxima of that sweep are reduced across the
@@ -2414,20 +2414,78 @@ hipError_t launch_slice_order(hipStream_t st, const int32_t* rp, Tiles tl, const
   return hipGetLastError();
 }
 
-// One wavefront per slice: copy each lane's row into the slice (value 0 and
-// column 0 past the row's end) and its diagonal entry (1 where no row).
-template <typename T>
-__global__ __launch_bounds__(BS) void k_slice_fill(MatView<T> m, Tiles tl, const int32_t* __restrict__ stile,
-                                                   int32_t nslice, const int32_t* __restrict__ off,
-                                                   const int32_t* __restrict__ width, const int32_t* __restrict__ row,
-                                                   T* __restrict__ d, T* __restrict__ val, uint16_t* __restrict__ c16,
-                                                   int32_t* __restrict__ c32) {
+// One wavefront per slice of a band tile: how many of its entries lie outside
+// the tile's window.
+__global__ __launch_bounds__(BS) void k_slice_far(const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                  Tiles tl, const int32_t* __restrict__ stile, int32_t nslice,
+                                                  const int32_t* __restrict__ row, int32_t* __restrict__ nfar) {
   const int s = blockIdx.x * (BS / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (s >= nslice) return;
   const int t = stile[s];
+  int n = 0;
+  if (tl.kind[t] == WIN_BAND) {
+    const int w0 = tl.w0[t], nw = tl.nw[t];
+    const int r = row[(size_t)s * SLICE + lane];
+    if (r >= 0)
+      for (int k = rp[r]; k < rp[r + 1]; k++) n += (unsigned)(col[k] - w0) >= (unsigned)nw;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+  }
+  if (lane == 0) nfar[s] = n;
+}
+hipError_t launch_slice_far(hipStream_t st, const int32_t* rp, const int32_t* col, Tiles tl, const int32_t* stile,
+                            int32_t nslice, const int32_t* row, int32_t* nfar) {
+  if (nslice <= 0) return hipSuccess;
+  k_slice_far<<<(unsigned)((nslice + BS / 64 - 1) / (BS / 64)), BS, 0, st>>>(rp, col, tl, stile, nslice, row, nfar);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(BS) void k_inexact32(const double* __restrict__ val, int64_t z, int32_t* inexact) {
+  bool bad = false;
+  for (int64_t k = (int64_t)blockIdx.x * BS + threadIdx.x; k < z; k += (int64_t)gridDim.x * BS)
+    bad = bad || (double)(float)val[k] != val[k];
+  if (__ballot(bad) && (threadIdx.x & 63) == 0) *inexact = 1;
+}
+hipError_t launch_inexact32(hipStream_t st, const double* val, int64_t z, int32_t* inexact) {
+  if (z <= 0) return hipSuccess;
+  k_inexact32<<<(unsigned)min((z + BS - 1) / BS, (int64_t)2048), BS, 0, st>>>(val, z, inexact);
+  return hipGetLastError();
+}
+
+// One wavefront per slice: copy each lane's row into the slice (value 0 and
+// column 0 past the row's end), its diagonal entry (1 where no row), its row
+// number and the slice's record; the wavefront after the last slice writes the
+// slice of no rows and the slots of zeros.
+template <typename T>
+__global__ __launch_bounds__(BS) void k_slice_fill(MatView<T> m, Tiles tl, const int32_t* __restrict__ stile,
+                                                   Sliced<T> sl, const int32_t* __restrict__ far0,
+                                                   const int32_t* __restrict__ nfar) {
+  const int s = blockIdx.x * (BS / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (s > sl.nslice) return;
+  T* d = const_cast<T*>(sl.d);
+  T* val = const_cast<T*>(sl.val);
+  float* val32 = const_cast<float*>(sl.val32);
+  uint16_t* c16 = const_cast<uint16_t*>(sl.c16);
+  int32_t* c32 = const_cast<int32_t*>(sl.c32);
+  uint16_t* r16 = const_cast<uint16_t*>(sl.r16);
+  int32_t* far = const_cast<int32_t*>(sl.far);
+  auto put = [&](size_t slot, T v) {
+    if (val) val[slot] = v;
+    else val32[slot] = (float)v;
+  };
+  if (s == sl.nslice) {
+    d[(size_t)s * SLICE + lane] = (T)1;
+    r16[(size_t)s * SLICE + lane] = 0xFFFF;
+    put((size_t)sl.nslot + lane, (T)0);
+    if (c16) c16[(size_t)sl.nslot + lane] = 0;
+    if (c32) c32[(size_t)sl.nslot + lane] = 0;
+    return;
+  }
+  const int t = stile[s];
   const int w0 = tl.w0[t];
-  const bool whole = tl.kind[t] == WIN_WHOLE;
-  const int r = row[(size_t)s * SLICE + lane];
+  const unsigned nw = (unsigned)tl.nw[t];
+  const bool whole = tl.kind[t] == WIN_WHOLE, wide = sl.wide[t] != 0;
+  const int r = sl.row[(size_t)s * SLICE + lane];
   int k0 = 0, len = 0;
   T dr = (T)1;
   if (r >= 0) {
@@ -2436,8 +2494,10 @@ __global__ __launch_bounds__(BS) void k_slice_fill(MatView<T> m, Tiles tl, const
     dr = m.d[r];
   }
   d[(size_t)s * SLICE + lane] = dr;
-  const int W = width[s];
-  const size_t o = (size_t)off[s] + lane;
+  r16[(size_t)s * SLICE + lane] = r >= 0 ? (uint16_t)(r - tl.row0[t]) : (uint16_t)0xFFFF;
+  const int W = sl.width[s], f0 = far0[s];
+  const size_t o = (size_t)sl.off[s] + lane;
+  int f = 0;
   for (int j = 0; j < W; j++) {
     const size_t slot = o + (size_t)j * SLICE;
     T v = (T)0;
@@ -2446,31 +2506,42 @@ __global__ __launch_bounds__(BS) void k_slice_fill(MatView<T> m, Tiles tl, const
       v = m.val[k0 + j];
       cr = whole ? (int)m.c16[k0 + j] : m.col[k0 + j] - w0;
     }
-    val[slot] = v;
-    if (whole) c16[slot] = (uint16_t)cr;
-    else c32[slot] = cr;
+    put(slot, v);
+    if (wide) {
+      c32[slot] = cr;
+      continue;
+    }
+    const bool out = (unsigned)cr >= nw;
+    const unsigned long long b = __ballot(out);
+    if (out) {
+      const int i = f + __popcll(b & ((1ull << lane) - 1ull));
+      far[f0 + i] = cr + w0;
+      cr = SLICE_FAR | i;
+    }
+    f += __popcll(b);
+    c16[slot] = (uint16_t)cr;
+  }
+  const bool unit = __ballot(dr != (T)1) == 0;
+  if (lane == 0) {
+    constexpr int NW = TNT / 64;
+    const int sb = sl.t_s0[t], n = sl.t_s0[t + 1] - sb, w = (s - sb) % NW;
+    SliceRec* rec = const_cast<SliceRec*>(sl.rec) + sb + w * (n / NW) + min(w, n % NW) + (s - sb) / NW;
+    *rec = SliceRec{sl.off[s], W | (unit ? SLICE_UNIT : 0), f0, nfar[s]};
   }
 }
 template <typename T>
-hipError_t launch_slice_fill(hipStream_t st, MatView<T> m, Tiles tl, const int32_t* stile, int32_t nslice,
-                             const int32_t* off, const int32_t* width, const int32_t* row, T* d, T* val,
-                             uint16_t* c16, int32_t* c32) {
-  if (nslice <= 0) return hipSuccess;
-  const unsigned g = (unsigned)((nslice + BS / 64 - 1) / (BS / 64));
-  k_slice_fill<T><<<g, BS, 0, st>>>(m, tl, stile, nslice, off, width, row, d, val, c16, c32);
+hipError_t launch_slice_fill(hipStream_t st, MatView<T> m, Tiles tl, const int32_t* stile, Sliced<T> sl,
+                             const int32_t* far0, const int32_t* nfar) {
+  if (sl.nslice <= 0) return hipSuccess;
+  const unsigned g = (unsigned)((sl.nslice + 1 + BS / 64 - 1) / (BS / 64));
+  k_slice_fill<T><<<g, BS, 0, st>>>(m, tl, stile, sl, far0, nfar);
   return hipGetLastError();
 }
-template hipError_t launch_slice_fill<double>(hipStream_t, MatView<double>, Tiles, const int32_t*, int32_t,
-                                              const int32_t*, const int32_t*, const int32_t*, double*, double*,
-                                              uint16_t*, int32_t*);
-template hipError_t launch_slice_fill<float>(hipStream_t, MatView<float>, Tiles, const int32_t*, int32_t,
-                                             const int32_t*, const int32_t*, const int32_t*, float*, float*,
-                                             uint16_t*, int32_t*);
+template hipError_t launch_slice_fill<double>(hipStream_t, MatView<double>, Tiles, const int32_t*, Sliced<double>,
+                                              const int32_t*, const int32_t*);
+template hipError_t launch_slice_fill<float>(hipStream_t, MatView<float>, Tiles, const int32_t*, Sliced<float>,
+                                             const int32_t*, const int32_t*);
 
-// NS slices per wavefront at a time (independent sums), their entries loaded
-// U per slice before any is used; the slice bounds are wavefront-uniform, so
-// the guards are scalar branches and padding past a slice's width is never
-// read.
 // ---- column panels of the sliced rows ---------------------------------------
 // Lane mask of the lanes below this one.
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
@@ -2736,90 +2807,210 @@ __device__ __forceinline__ void spmv_panel_rows(const Sliced<T>& sl, T* __restri
   }
 }
 
-template <typename T, int U, int NS>
-struct SliceGroup {
-  int off[NS], W[NS], row[NS], Wm;
-  T d[NS];
-  T vv[NS][U];
+// Slices and entries of each under way at a time.  SKIP: no load past a slice's
+// width or a wavefront's last slice (a branch each); else those loads read zeros.
+// NARROW sets have slices of up to about four entries, so that one chunk holds a
+// slice.  us per sweep, narrow / wide shape: 33.5 M-state program graph (3
+// entries per row) FP64 451 / 580, FP32 350 / 406; 64 chains of 20,000 (7.3 per
+// row) FP64 34.1 / 28.0, FP32 19.8 / 18.3; 500 chains of 16,000 (4.5 per row; wide)
+// FP64 137 / 127, FP32 75.7 / 72.6.  Reading zeros is slower in FP32 also on narrow
+// slices (357).  In FP64 8 x 2 sweeps the last at 120, but the 64 chains at 29.6.
+template <typename T, bool NARROW>
+struct SliceShape;
+template <>
+struct SliceShape<double, false> {  // one 1024-thread block per CU: registers to spare
+  static constexpr int U = 4, NS = 4;
+  static constexpr bool SKIP = true;
+};
+template <>
+struct SliceShape<double, true> {
+  static constexpr int U = 4, NS = 4;
+  static constexpr bool SKIP = false;
+};
+template <>
+struct SliceShape<float, false> {  // two blocks per CU: at most 64 VGPRs
+  static constexpr int U = 8, NS = 1;
+  static constexpr bool SKIP = true;
+};
+template <>
+struct SliceShape<float, true> {
+  static constexpr int U = 4, NS = 2;
+  static constexpr bool SKIP = true;
+};
+
+// Columns of a slice's entries in the sweeps: 16-bit all inside the window (the
+// whole block), 16-bit with far ones (a band), or 32-bit (no window: nw = 0, or
+// a wide band tile).
+enum { COL_IN = 0, COL_FAR = 1, COL_WIDE = 2 };
+template <typename T, typename VT>
+__device__ __forceinline__ const VT* slice_values(const Sliced<T>& sl) {
+  if constexpr (std::is_same<VT, T>::value) return sl.val;
+  else return sl.val32;
+}
+
+// A wavefront's slices of a tile, taken NS at a time in the order of their
+// records.  The sweep is bound by the memory rate as long as enough loads are
+// under way, and with one block per compute unit (an FP64 window fills its LDS)
+// that is a question of how many loads wait for others: the records are read
+// once, a lane each, before the window is staged, the row numbers (and the
+// columns of far entries) of the next slices while the current ones' entries
+// are under way, so that a group of NS slices costs one memory latency instead
+// of three, and no load is conditional (a compiler's wait after a branch is a
+// wait for all loads).  Fewer bytes come second: 16-bit rows and columns, no
+// diagonal where it is 1, FP64 values that FP32 holds exactly in 4 bytes; far
+// entries' x are gathered by one load per slice, a lane each, and handed to
+// their rows with a lane permute.  us per sweep, before (row numbers, then rhs; scalar widths,
+// then entries; 4-byte row numbers and band columns; every diagonal) -> now:
+// 33.5 M-state program graph FP64 608 -> 451 (4.1 TB/s of what is now read), FP32
+// 426 -> 350; 2 M states 29.7 -> 22.9, 21.7 -> 18.9; 500 chains of 16,000 137 ->
+// 127, 77 -> 72.6; 64 chains of 20,000 29.2 -> 28.0, 19.0 -> 18.3.  Fewer bytes
+// without the order of the loads made the first one slower (706).  The path by
+// column form is chosen after the window is staged: chosen before, its threefold
+// code took 5 us more per FP32 launch.
+template <typename T, bool NARROW>
+struct SliceRows {
+  static constexpr int U = SliceShape<T, NARROW>::U, NS = SliceShape<T, NARROW>::NS, NW = TNT / 64;
+  static constexpr bool SKIP = SliceShape<T, NARROW>::SKIP;
+  SliceRec m;  // of the wavefront's slice `lane`
+  int wave, lane, sb, n;
+  int next_row[NS], next_far[NS];  // of the next group
+
+  // band: the slices may have far entries
+  __device__ __forceinline__ SliceRows(const Sliced<T>& sl, int sb_, int se, bool band) {
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lane = threadIdx.x & 63;
+    sb = sb_;
+    const int ns = se - sb, per = ns / NW, rem = ns % NW;
+    n = per + (wave < rem ? 1 : 0);
+    m = SliceRec{0, SLICE_UNIT, 0, 0};
+    if (lane < n) m = sl.rec[sb + wave * per + min(wave, rem) + lane];
+    rows(sl, 0);
+    if (band) far(sl, 0);
+  }
+  // row numbers (0xFFFF: none) and columns of far entries of group i
+  __device__ __forceinline__ void rows(const Sliced<T>& sl, int i) {
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+      const bool ok = i + q < n;
+      next_row[q] = 0xFFFF;
+      if (!SKIP || ok) next_row[q] = sl.r16[(size_t)(ok ? sb + wave + (i + q) * NW : sl.nslice) * SLICE + lane];
+    }
+  }
+  __device__ __forceinline__ void far(const Sliced<T>& sl, int i) {
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+      const int e = (i + q) & 63, f0 = __builtin_amdgcn_readlane(m.far0, e), nf = __builtin_amdgcn_readlane(m.nfar, e);
+      next_far[q] = sl.far[i + q < n && lane < nf ? f0 + lane : 0];
+    }
+  }
+};
+template <typename T, typename VT, int COL, bool NT, bool NARROW>
+struct SlicePipe : SliceRows<T, NARROW> {
+  using R = SliceRows<T, NARROW>;
+  using R::U, R::NS, R::NW, R::SKIP, R::m, R::wave, R::lane, R::sb, R::n, R::next_row, R::next_far;
+  int row[NS];  // of the group being swept
+  int off[NS], W[NS], Wm, nfar[NS];
+  bool unit[NS];
+  T d[NS], xf[NS];
+  VT vv[NS][U];
   int cc[NS][U];
 
-  __device__ __forceinline__ void setup(const Sliced<T>& sl, int s0, int se, int lane) {
-    constexpr int NW = TNT / 64;
+  __device__ __forceinline__ explicit SlicePipe(const R& r) : R(r) {}
+  __device__ __forceinline__ void next(const Sliced<T>& sl, int i) {
+    R::rows(sl, i);
+    if (COL == COL_FAR) R::far(sl, i);
+  }
+  // group i becomes the current one: its first entries, diagonal and far x are
+  // read (rhs is read by the caller, at row0 + row), and then the next rows
+  __device__ __forceinline__ void begin(const Sliced<T>& sl, const T* __restrict__ x, int i) {
     Wm = 0;
 #pragma unroll
     for (int q = 0; q < NS; q++) {
-      const int s = s0 + q * NW;
-      const bool ok = s < se;
-      off[q] = ok ? sl.off[s] : 0;
-      W[q] = ok ? sl.width[s] : 0;
-      row[q] = ok ? sl.row[(size_t)s * SLICE + lane] : -1;
-      d[q] = ok ? sl.d[(size_t)s * SLICE + lane] : (T)1;
+      const int e = (i + q) & 63;
+      const bool ok = i + q < n;
+      const int w = ok ? __builtin_amdgcn_readlane(m.width, e) : SLICE_UNIT;
+      off[q] = __builtin_amdgcn_readlane(m.off, e);
+      W[q] = w & (SLICE_UNIT - 1);
+      unit[q] = (w & SLICE_UNIT) != 0;
+      nfar[q] = COL == COL_FAR && ok ? __builtin_amdgcn_readlane(m.nfar, e) : 0;
       Wm = max(Wm, W[q]);
+      row[q] = next_row[q];
+      if (COL == COL_FAR) xf[q] = x[next_far[q]];
+      d[q] = (T)1;
+      if (!SKIP || !unit[q]) d[q] = sl.d[(size_t)(unit[q] ? sl.nslice : sb + wave + (i + q) * NW) * SLICE + lane];
     }
+    load(sl, 0);
   }
-  template <int KIND, bool NT>
-  __device__ __forceinline__ void chunk(const Sliced<T>& sl, int j, int lane) {
+  __device__ __forceinline__ void load(const Sliced<T>& sl, int j) {
+    const VT* __restrict__ val = slice_values<T, VT>(sl);
 #pragma unroll
     for (int q = 0; q < NS; q++)
 #pragma unroll
       for (int u = 0; u < U; u++) {
-        vv[q][u] = 0;
-        cc[q][u] = 0;
-        if (j + u < W[q]) {
-          const size_t k = (size_t)off[q] + (size_t)(j + u) * SLICE + lane;
-          if (NT) {
-            vv[q][u] = __builtin_nontemporal_load(sl.val + k);
-            cc[q][u] = KIND == WIN_WHOLE ? (int)__builtin_nontemporal_load(sl.c16 + k)
-                                         : __builtin_nontemporal_load(sl.c32 + k);
-          } else {
-            vv[q][u] = sl.val[k];
-            cc[q][u] = KIND == WIN_WHOLE ? (int)sl.c16[k] : sl.c32[k];
-          }
+        const bool in = j + u < W[q];
+        if (SKIP) {
+          vv[q][u] = 0;
+          cc[q][u] = 0;
+          if (!in) continue;
+        }
+        const size_t k = (size_t)(in ? off[q] + (j + u) * SLICE : sl.nslot) + lane;
+        if (NT) {
+          vv[q][u] = __builtin_nontemporal_load(val + k);
+          cc[q][u] = COL == COL_WIDE ? __builtin_nontemporal_load(sl.c32 + k)
+                                     : (int)__builtin_nontemporal_load(sl.c16 + k);
+        } else {
+          vv[q][u] = val[k];
+          cc[q][u] = COL == COL_WIDE ? sl.c32[k] : (int)sl.c16[k];
         }
       }
   }
+  __device__ __forceinline__ void add(T acc[NS], const T* __restrict__ xs, const T* __restrict__ x, int nw, int w0) {
+#pragma unroll
+    for (int q = 0; q < NS; q++) {
+      if (COL == COL_FAR && nfar[q] > 0) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          const int c = cc[q][u];
+          const T xo = __shfl(xf[q], c & 63, 64), xi = xs[c & (SLICE_FAR - 1)];
+          acc[q] += (T)vv[q][u] * ((c & SLICE_FAR) ? xo : xi);
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; u++) acc[q] += (T)vv[q][u] * xget<COL == COL_WIDE ? WIN_BAND : WIN_WHOLE>(xs, x, cc[q][u], nw, w0);
+      }
+    }
+  }
 };
 
-template <typename T>
-struct SliceShape;
-template <>
-struct SliceShape<double> {  // one 1024-thread block per CU: registers to spare
-  static constexpr int U = 4, NS = 4;
-};
-template <>
-struct SliceShape<float> {  // two blocks per CU: at most 64 VGPRs
-  static constexpr int U = 8, NS = 1;
-};
-
-template <typename T, int KIND, bool NT>
-__device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const T* __restrict__ rhs,
-                                                     const T* __restrict__ xs, const T* __restrict__ x,
-                                                     T* __restrict__ xn, int sb, int se, int w0, int nw, int weighted) {
-  constexpr int U = SliceShape<T>::U, NS = SliceShape<T>::NS, NW = TNT / 64;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+// Jacobi rows of a tile's slices.
+template <typename T, typename VT, int COL, bool NT, bool NARROW>
+__device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const SliceRows<T, NARROW>& rows,
+                                                     const T* __restrict__ rhs, const T* __restrict__ xs,
+                                                     const T* __restrict__ x, T* __restrict__ xn, int row0, int w0,
+                                                     int nw, int weighted) {
+  constexpr int U = SliceRows<T, NARROW>::U, NS = SliceRows<T, NARROW>::NS;
   double mloc = 0.0;
-  for (int s0 = sb + wave; s0 < se; s0 += NW * NS) {
-    SliceGroup<T, U, NS> g;
-    g.setup(sl, s0, se, lane);
+  SlicePipe<T, VT, COL, NT, NARROW> g(rows);
+  for (int i = 0; i < g.n; i += NS) {
     T b[NS], acc[NS];
 #pragma unroll
     for (int q = 0; q < NS; q++) {
-      b[q] = (rhs && g.row[q] >= 0) ? rhs[g.row[q]] : (T)0;
+      b[q] = rhs && (!g.SKIP || i + q < g.n) ? rhs[row0 + (g.next_row[q] != 0xFFFF ? g.next_row[q] : 0)] : (T)0;
       acc[q] = 0;
     }
-    for (int j = 0; j < g.Wm; j += U) {
-      g.template chunk<KIND, NT>(sl, j, lane);
-#pragma unroll
-      for (int q = 0; q < NS; q++)
-#pragma unroll
-        for (int u = 0; u < U; u++) acc[q] += g.vv[q][u] * xget<KIND>(xs, x, g.cc[q][u], nw, w0);
+    g.begin(sl, x, i);
+    g.next(sl, i + NS);
+    g.add(acc, xs, x, nw, w0);
+    for (int j = U; j < g.Wm; j += U) {
+      g.load(sl, j);
+      g.add(acc, xs, x, nw, w0);
     }
 #pragma unroll
     for (int q = 0; q < NS; q++) {
-      const int row = g.row[q];
-      if (row >= 0) {
-        const T nv = (b[q] + acc[q]) / g.d[q];
-        const double dl = fabs((double)nv - (double)xget<KIND>(xs, x, row - w0, nw, w0));
+      if (g.row[q] != 0xFFFF) {
+        const int row = row0 + g.row[q];
+        const T nv = g.unit[q] ? b[q] + acc[q] : (b[q] + acc[q]) / g.d[q];
+        const double dl = fabs((double)nv - (double)xget<COL == COL_WIDE ? WIN_BAND : WIN_WHOLE>(xs, x, row - w0, nw, w0));
         xn[row] = nv;
         mloc = mx(mloc, weighted ? (double)g.d[q] * dl : dl);
       }
@@ -2828,7 +3019,7 @@ __device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const 
   return mloc;
 }
 
-template <typename T, bool NT, bool PANEL>
+template <typename T, bool NT, bool PANEL, bool NARROW, typename VT>
 __global__ __launch_bounds__(TNT) void k_jacobi_sliced(Sliced<T> sl, const T* __restrict__ rhs,
                                                        const T* __restrict__ x, T* __restrict__ xn, Tiles tl, int64_t s_rel,
                                                        const double* __restrict__ pprev, double* __restrict__ pcur,
@@ -2843,16 +3034,25 @@ __global__ __launch_bounds__(TNT) void k_jacobi_sliced(Sliced<T> sl, const T* __
   const int sb = sl.t_s0[c], se = sl.t_s0[c + 1];
   if (status[inst] != ST_RUN) return;
   const int64_t s = s_rel + (tl.sbase ? *tl.sbase : 0);
+  const int r0 = tl.row0[c], wide = sl.wide[c];
+  const SliceRows<T, NARROW> rows(sl, sb, se, kind == WIN_BAND);
   if (!jacobi_begin<T>(xs, x, tl, c, inst, kind, w0, nw, s, pprev, status, iters, meas, thr, strict, max_iter, ndone))
     return;
   double mloc;
   if (PANEL && sl.npan[c] > 0) mloc = jacobi_panel_rows<T>(sl, rhs, xs, x, xn, c, sb, se, w0, weighted);
-  else if (kind == WIN_WHOLE) mloc = jacobi_sliced_rows<T, WIN_WHOLE, NT>(sl, rhs, xs, x, xn, sb, se, w0, nw, weighted);
-  else if (kind == WIN_BAND) mloc = jacobi_sliced_rows<T, WIN_BAND, NT>(sl, rhs, xs, x, xn, sb, se, w0, nw, weighted);
-  else mloc = jacobi_sliced_rows<T, WIN_NONE, NT>(sl, rhs, xs, x, xn, sb, se, w0, nw, weighted);
+  else if (wide) mloc = jacobi_sliced_rows<T, VT, COL_WIDE, NT, NARROW>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
+  else if (kind == WIN_WHOLE) mloc = jacobi_sliced_rows<T, VT, COL_IN, NT, NARROW>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
+  else mloc = jacobi_sliced_rows<T, VT, COL_FAR, NT, NARROW>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
   double v[1] = {mloc};
   block_reduce<1, TNT>(v, 1u);
   if (threadIdx.x == 0) pcur[c] = v[0];
+}
+
+// Which instance of the sliced kernels: streamed or not, and paneled (never
+// narrow), or narrow and with FP32 values or not.
+template <typename T>
+static int slice_variant(const Sliced<T>& sl) {
+  return (sl.stream ? 1 : 0) + (sl.paneled ? 2 : (sl.val32 ? (sl.narrow ? 8 : 4) : (sl.narrow ? 6 : 0)));
 }
 
 template <typename T>
@@ -2860,10 +3060,13 @@ hipError_t launch_jacobi_sliced(hipStream_t st, Sliced<T> sl, const T* rhs, cons
                                 const double* pprev, double* pcur, int32_t* status, int64_t* iters, double* meas,
                                 const double* thr, int strict, int64_t max_iter, int32_t* ndone, int weighted) {
   const size_t lds = (size_t)max(tl.maxw, sl.paneled ? sl.pw : 0) * sizeof(T);
-  static size_t conf[4] = {0, 0, 0, 0};
-  const int v = (sl.stream ? 1 : 0) + (sl.paneled ? 2 : 0);
-  const auto kern = v == 0 ? k_jacobi_sliced<T, false, false> : v == 1 ? k_jacobi_sliced<T, true, false>
-                  : v == 2 ? k_jacobi_sliced<T, false, true> : k_jacobi_sliced<T, true, true>;
+  static size_t conf[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const int v = slice_variant(sl);
+  const auto kern = v == 0 ? k_jacobi_sliced<T, false, false, false, T> : v == 1 ? k_jacobi_sliced<T, true, false, false, T>
+                  : v == 2 ? k_jacobi_sliced<T, false, true, false, T> : v == 3 ? k_jacobi_sliced<T, true, true, false, T>
+                  : v == 4 ? k_jacobi_sliced<T, false, false, false, float> : v == 5 ? k_jacobi_sliced<T, true, false, false, float>
+                  : v == 6 ? k_jacobi_sliced<T, false, false, true, T> : v == 7 ? k_jacobi_sliced<T, true, false, true, T>
+                  : v == 8 ? k_jacobi_sliced<T, false, false, true, float> : k_jacobi_sliced<T, true, false, true, float>;
   hipError_t e = set_lds(kern, lds, conf[v]);
   if (e != hipSuccess) return e;
   kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, rhs, x, xn, tl, s, pprev, pcur, status, iters, meas, thr, strict,
@@ -2885,44 +3088,64 @@ template hipError_t launch_jacobi_sliced<float>(hipStream_t, Sliced<float>, cons
 // sliced sweep's bit for bit, and U x NS entries of different slices are in
 // flight where one lane per row would wait on a long row's entries one
 // after another.
-template <typename T>
+template <typename T, typename VT>
 __device__ __forceinline__ double resident_sliced_rows(const Sliced<T>& sl, const T* __restrict__ rhs,
                                                        const T* cur, T* nxt, int sb, int se, int r0,
                                                        int weighted) {
-  constexpr int U = SliceShape<T>::U, NS = SliceShape<T>::NS, NW = TNT / 64;
+  constexpr int U = SliceShape<T, false>::U, NS = SliceShape<T, false>::NS, NW = TNT / 64;
+  const VT* __restrict__ val = slice_values<T, VT>(sl);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   double mloc = 0.0;
   for (int s0 = sb + wave; s0 < se; s0 += NW * NS) {
-    SliceGroup<T, U, NS> g;
-    g.setup(sl, s0, se, lane);
-    T b[NS], acc[NS];
+    int off[NS], W[NS], rows[NS], Wm = 0;
+    T d[NS], b[NS], acc[NS];
 #pragma unroll
     for (int q = 0; q < NS; q++) {
-      b[q] = (rhs && g.row[q] >= 0) ? rhs[g.row[q]] : (T)0;
+      const int s = s0 + q * NW;
+      const bool ok = s < se;
+      off[q] = ok ? sl.off[s] : 0;
+      W[q] = ok ? sl.width[s] : 0;
+      rows[q] = ok ? sl.row[(size_t)s * SLICE + lane] : -1;
+      d[q] = ok ? sl.d[(size_t)s * SLICE + lane] : (T)1;
+      b[q] = (rhs && rows[q] >= 0) ? rhs[rows[q]] : (T)0;
       acc[q] = 0;
+      Wm = max(Wm, W[q]);
     }
-    for (int j = 0; j < g.Wm; j += U) {
-      g.template chunk<WIN_WHOLE, false>(sl, j, lane);
+    for (int j = 0; j < Wm; j += U) {
+      VT vv[NS][U];
+      int cc[NS][U];
 #pragma unroll
       for (int q = 0; q < NS; q++)
 #pragma unroll
-        for (int u = 0; u < U; u++) acc[q] += g.vv[q][u] * cur[g.cc[q][u]];
+        for (int u = 0; u < U; u++) {
+          vv[q][u] = 0;
+          cc[q][u] = 0;
+          if (j + u < W[q]) {
+            const size_t k = (size_t)off[q] + (size_t)(j + u) * SLICE + lane;
+            vv[q][u] = val[k];
+            cc[q][u] = sl.c16[k];
+          }
+        }
+#pragma unroll
+      for (int q = 0; q < NS; q++)
+#pragma unroll
+        for (int u = 0; u < U; u++) acc[q] += (T)vv[q][u] * cur[cc[q][u]];
     }
 #pragma unroll
     for (int q = 0; q < NS; q++) {
-      const int row = g.row[q];
+      const int row = rows[q];
       if (row >= 0) {
-        const T nv = (b[q] + acc[q]) / g.d[q];
+        const T nv = (b[q] + acc[q]) / d[q];
         const double dl = fabs((double)nv - (double)cur[row - r0]);
         nxt[row - r0] = nv;
-        mloc = mx(mloc, weighted ? (double)g.d[q] * dl : dl);
+        mloc = mx(mloc, weighted ? (double)d[q] * dl : dl);
       }
     }
   }
   return mloc;
 }
 
-template <typename T>
+template <typename T, typename VT>
 __global__ __launch_bounds__(TNT) void k_jacobi_resident_sliced(Sliced<T> sl, const T* __restrict__ rhs, T* xa, T* xb,
                                                                 Tiles tl, const int32_t* __restrict__ s_lo,
                                                                 const int32_t* __restrict__ s_hi, int64_t s0,
@@ -2944,7 +3167,7 @@ __global__ __launch_bounds__(TNT) void k_jacobi_resident_sliced(Sliced<T> sl, co
   for (int it = 0; it < nsweeps; it++) {
     const T* cur = (it & 1) ? X1 : X0;
     T* nxt = (it & 1) ? X0 : X1;
-    double v[1] = {resident_sliced_rows<T>(sl, rhs, cur, nxt, sb, se, r0, weighted)};
+    double v[1] = {resident_sliced_rows<T, VT>(sl, rhs, cur, nxt, sb, se, r0, weighted)};
     block_reduce<1, TNT>(v, 1u);
     const int64_t done = s0 + it + 1;  // sweeps completed
     if (threadIdx.x == 0) {
@@ -2983,12 +3206,12 @@ hipError_t launch_jacobi_resident_sliced(hipStream_t st, Sliced<T> sl, const T* 
                                          int strict, int64_t max_iter, int32_t* ndone, int weighted) {
   if (tl.ntile <= 0 || nsweeps <= 0) return hipSuccess;
   const size_t lds = 2 * (size_t)tl.maxw * sizeof(T);
-  static size_t conf = 0;
-  hipError_t e = set_lds(k_jacobi_resident_sliced<T>, lds, conf);
+  static size_t conf[2] = {0, 0};
+  const auto kern = sl.val32 ? k_jacobi_resident_sliced<T, float> : k_jacobi_resident_sliced<T, T>;
+  hipError_t e = set_lds(kern, lds, conf[sl.val32 ? 1 : 0]);
   if (e != hipSuccess) return e;
-  k_jacobi_resident_sliced<T><<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, rhs, xa, xb, tl, s_lo, s_hi, s0, nsweeps,
-                                                                    status, iters, meas, thr, strict, max_iter,
-                                                                    ndone, weighted);
+  kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, rhs, xa, xb, tl, s_lo, s_hi, s0, nsweeps, status, iters, meas, thr,
+                                             strict, max_iter, ndone, weighted);
   return hipGetLastError();
 }
 template hipError_t launch_jacobi_resident_sliced<double>(hipStream_t, Sliced<double>, const double*, double*,
@@ -3003,38 +3226,39 @@ template hipError_t launch_jacobi_resident_sliced<float>(hipStream_t, Sliced<flo
 // y = d u - A_off u on sliced rows, with the dot products of the lane-group
 // kernel (MODE 0: q.y; MODE 1: y.u and y.y), or (MODE 2) the FP64 residual
 // y <- qv - y of the refinement with its max |.| (qv is then b).
-template <typename T, int MODE, int KIND, bool NT>
-__device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const T* __restrict__ us,
-                                                 const T* __restrict__ u, T* __restrict__ y, const T* __restrict__ qv,
-                                                 int sb, int se, int w0, int nw, double* a) {
-  constexpr int U = SliceShape<T>::U, NS = SliceShape<T>::NS, NW = TNT / 64;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  for (int s0 = sb + wave; s0 < se; s0 += NW * NS) {
-    SliceGroup<T, U, NS> g;
-    g.setup(sl, s0, se, lane);
-    T acc[NS];
+template <typename T, typename VT, int MODE, int COL, bool NT, bool NARROW>
+__device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const SliceRows<T, NARROW>& rows,
+                                                 const T* __restrict__ us, const T* __restrict__ u, T* __restrict__ y,
+                                                 const T* __restrict__ qv, int row0, int w0, int nw, double* a) {
+  constexpr int U = SliceRows<T, NARROW>::U, NS = SliceRows<T, NARROW>::NS;
+  SlicePipe<T, VT, COL, NT, NARROW> g(rows);
+  for (int i = 0; i < g.n; i += NS) {
+    T b[NS], acc[NS];
 #pragma unroll
-    for (int q = 0; q < NS; q++) acc[q] = 0;
-    for (int j = 0; j < g.Wm; j += U) {
-      g.template chunk<KIND, NT>(sl, j, lane);
-#pragma unroll
-      for (int q = 0; q < NS; q++)
-#pragma unroll
-        for (int k = 0; k < U; k++) acc[q] += g.vv[q][k] * xget<KIND>(us, u, g.cc[q][k], nw, w0);
+    for (int q = 0; q < NS; q++) {
+      b[q] = MODE != 1 && (!g.SKIP || i + q < g.n) ? qv[row0 + (g.next_row[q] != 0xFFFF ? g.next_row[q] : 0)] : (T)0;
+      acc[q] = 0;
+    }
+    g.begin(sl, u, i);
+    g.next(sl, i + NS);
+    g.add(acc, us, u, nw, w0);
+    for (int j = U; j < g.Wm; j += U) {
+      g.load(sl, j);
+      g.add(acc, us, u, nw, w0);
     }
 #pragma unroll
     for (int q = 0; q < NS; q++) {
-      const int row = g.row[q];
-      if (row >= 0) {
-        const T ui = xget<KIND>(us, u, row - w0, nw, w0);
+      if (g.row[q] != 0xFFFF) {
+        const int row = row0 + g.row[q];
+        const T ui = xget<COL == COL_WIDE ? WIN_BAND : WIN_WHOLE>(us, u, row - w0, nw, w0);
         const T yi = g.d[q] * ui - acc[q];
         if (MODE == 2) {
-          const T ri = qv[row] - yi;
+          const T ri = b[q] - yi;
           y[row] = ri;
           a[0] = mx(a[0], fabs((double)ri));
         } else if (MODE == 0) {
           y[row] = yi;
-          a[0] += (double)qv[row] * (double)yi;
+          a[0] += (double)b[q] * (double)yi;
         } else {
           y[row] = yi;
           a[0] += (double)yi * (double)ui;
@@ -3045,7 +3269,7 @@ __device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const T* _
   }
 }
 
-template <typename T, int MODE, bool NT, bool PANEL>
+template <typename T, int MODE, bool NT, bool PANEL, bool NARROW, typename VT>
 __global__ __launch_bounds__(TNT) void k_spmv_sliced(Sliced<T> sl, const T* __restrict__ u, T* __restrict__ y,
                                                      const T* __restrict__ qv, Tiles tl,
                                                      const int32_t* __restrict__ status, double* __restrict__ part) {
@@ -3055,15 +3279,17 @@ __global__ __launch_bounds__(TNT) void k_spmv_sliced(Sliced<T> sl, const T* __re
   if (status[tl.inst[c]] != ST_RUN) return;
   const int w0 = tl.w0[c], nw = tl.nw[c], kind = tl.kind[c];
   const int sb = sl.t_s0[c], se = sl.t_s0[c + 1];
+  const int r0 = tl.row0[c], wide = sl.wide[c];
+  const SliceRows<T, NARROW> rows(sl, sb, se, kind == WIN_BAND);
   if (kind != WIN_NONE) {
     stage_window<T, TNT>(us, u, w0, nw);
     __syncthreads();
   }
   double a[2] = {0.0, 0.0};
   if (PANEL && sl.npan[c] > 0) spmv_panel_rows<T, MODE>(sl, us, u, y, qv, c, sb, se, w0, a);
-  else if (kind == WIN_WHOLE) spmv_sliced_rows<T, MODE, WIN_WHOLE, NT>(sl, us, u, y, qv, sb, se, w0, nw, a);
-  else if (kind == WIN_BAND) spmv_sliced_rows<T, MODE, WIN_BAND, NT>(sl, us, u, y, qv, sb, se, w0, nw, a);
-  else spmv_sliced_rows<T, MODE, WIN_NONE, NT>(sl, us, u, y, qv, sb, se, w0, nw, a);
+  else if (wide) spmv_sliced_rows<T, VT, MODE, COL_WIDE, NT, NARROW>(sl, rows, us, u, y, qv, r0, w0, nw, a);
+  else if (kind == WIN_WHOLE) spmv_sliced_rows<T, VT, MODE, COL_IN, NT, NARROW>(sl, rows, us, u, y, qv, r0, w0, nw, a);
+  else spmv_sliced_rows<T, VT, MODE, COL_FAR, NT, NARROW>(sl, rows, us, u, y, qv, r0, w0, nw, a);
   if (MODE != 1) {
     double b1[1] = {a[0]};
     block_reduce<1, TNT>(b1, MODE == 2 ? 1u : 0u);
@@ -3081,10 +3307,13 @@ template <typename T, int MODE>
 static hipError_t spmv_sliced_M(hipStream_t st, Sliced<T> sl, const T* u, T* y, const T* qv, Tiles tl,
                                 const int32_t* status, double* part) {
   const size_t lds = (size_t)max(tl.maxw, sl.paneled ? sl.pw : 0) * sizeof(T);
-  static size_t conf[4] = {0, 0, 0, 0};
-  const int v = (sl.stream ? 1 : 0) + (sl.paneled ? 2 : 0);
-  const auto kern = v == 0 ? k_spmv_sliced<T, MODE, false, false> : v == 1 ? k_spmv_sliced<T, MODE, true, false>
-                  : v == 2 ? k_spmv_sliced<T, MODE, false, true> : k_spmv_sliced<T, MODE, true, true>;
+  static size_t conf[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const int v = slice_variant(sl);
+  const auto kern = v == 0 ? k_spmv_sliced<T, MODE, false, false, false, T> : v == 1 ? k_spmv_sliced<T, MODE, true, false, false, T>
+                  : v == 2 ? k_spmv_sliced<T, MODE, false, true, false, T> : v == 3 ? k_spmv_sliced<T, MODE, true, true, false, T>
+                  : v == 4 ? k_spmv_sliced<T, MODE, false, false, false, float> : v == 5 ? k_spmv_sliced<T, MODE, true, false, false, float>
+                  : v == 6 ? k_spmv_sliced<T, MODE, false, false, true, T> : v == 7 ? k_spmv_sliced<T, MODE, true, false, true, T>
+                  : v == 8 ? k_spmv_sliced<T, MODE, false, false, true, float> : k_spmv_sliced<T, MODE, true, false, true, float>;
   hipError_t e = set_lds(kern, lds, conf[v]);
   if (e != hipSuccess) return e;
   kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, u, y, qv, tl, status, part);
