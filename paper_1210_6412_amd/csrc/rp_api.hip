@@ -144,6 +144,8 @@ struct rp_context {
   hipStream_t cap_stream = nullptr;  // private stream that graphs are captured on (never run)
   std::string err;
   HostPinned pin;
+  HostPinned upin;                // host arrays on their way to the device (Uploads)
+  size_t upin_used = 0;
   bool prof = false;
   ProfStat stat[RP_PROF_NKERNELS];
   struct Pend {
@@ -485,6 +487,47 @@ void to_dev(rp_context* ctx, T* dev, const T* host, size_t count) {
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
 }
 
+// Host arrays to the device without a copy command and a synchronisation each
+// (about 12 us apiece; laying a system out takes some 50): add() copies them into
+// a pinned ring of the context, run() has one kernel read them from there.  A
+// region of the ring is used again only after a synchronisation.  Arrays larger
+// than a part go by copy.  run() must precede the first kernel that reads them.
+constexpr size_t kUploadPart = 64 * 1024, kUploadRing = 1024 * 1024;
+struct Uploads {
+  rp_context* ctx;
+  UploadTable t;
+  int parts = 0;
+  explicit Uploads(rp_context* c) : ctx(c) {}
+  Uploads(const Uploads&) = delete;
+  template <typename T>
+  void add(T* dev, const T* host, size_t count) {
+    static_assert(sizeof(T) % 4 == 0, "words");
+    if (count == 0) return;
+    const size_t bytes = count * sizeof(T);
+    if (bytes > kUploadPart) return to_dev(ctx, dev, host, count);
+    HIPCHK(ctx, ctx->upin.reserve(kUploadRing));
+    if (parts == UPLOAD_PARTS || ctx->upin_used + bytes > kUploadRing) {
+      run();
+      if (ctx->upin_used + bytes > kUploadRing) {
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        ctx->upin_used = 0;
+      }
+    }
+    std::memcpy(static_cast<unsigned char*>(ctx->upin.p) + ctx->upin_used, host, bytes);
+    t.dst[parts] = dev;
+    t.off[parts] = (uint32_t)ctx->upin_used;
+    t.bytes[parts++] = (uint32_t)bytes;
+    ctx->upin_used += (bytes + 15) / 16 * 16;
+  }
+  void run() {
+    if (parts == 0) return;
+    void* src = nullptr;
+    HIPCHK(ctx, hipHostGetDevicePointer(&src, ctx->upin.p, 0));
+    HIPCHK(ctx, launch_upload(ctx->stream, static_cast<const unsigned char*>(src), t, parts));
+    parts = 0;
+  }
+};
+
 // One device int32 read back without a copy command or a stream
 // synchronisation: a one-thread kernel stores it, with a sequence number, into
 // host-mapped pinned memory, and the host spins on the sequence number.  The
@@ -722,7 +765,7 @@ std::vector<int32_t> balanced_order(const std::vector<int32_t>& tc0, const std::
 }
 
 void build_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t width, int per_cu,
-                 const std::vector<int32_t>& hist) {
+                 const std::vector<int32_t>& hist, Uploads& up) {
   const int K = s->K;
   const int64_t np = s->npad;
   const int64_t wmax = (int64_t)(TILE_LDS_BYTES / width) / PAD * PAD;
@@ -864,13 +907,13 @@ void build_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t w
   dalloc(ctx, ts.w0, (size_t)nt);
   dalloc(ctx, ts.nw, (size_t)nt);
   dalloc(ctx, ts.kind, (size_t)nt);
-  to_dev(ctx, ts.row0.p, trow0.data(), (size_t)nt);
-  to_dev(ctx, ts.nrows.p, tnr.data(), (size_t)nt);
-  to_dev(ctx, ts.inst.p, tinst.data(), (size_t)nt);
-  to_dev(ctx, ts.inst0.p, tc0.data(), (size_t)K + 1);
-  to_dev(ctx, ts.w0.p, tw0.data(), (size_t)nt);
-  to_dev(ctx, ts.nw.p, tnw.data(), (size_t)nt);
-  to_dev(ctx, ts.kind.p, tkind.data(), (size_t)nt);
+  up.add(ts.row0.p, trow0.data(), (size_t)nt);
+  up.add(ts.nrows.p, tnr.data(), (size_t)nt);
+  up.add(ts.inst.p, tinst.data(), (size_t)nt);
+  up.add(ts.inst0.p, tc0.data(), (size_t)K + 1);
+  up.add(ts.w0.p, tw0.data(), (size_t)nt);
+  up.add(ts.nw.p, tnw.data(), (size_t)nt);
+  up.add(ts.kind.p, tkind.data(), (size_t)nt);
   ts.nrows_h = tnr;
   ts.nw_h = tnw;
   ts.kind_h = tkind;
@@ -879,7 +922,7 @@ void build_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t w
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, (int32_t)maxw};
   const std::vector<int32_t> order = balanced_order(tc0, tcost);
   dalloc(ctx, ts.order, (size_t)nt);
-  to_dev(ctx, ts.order.p, order.data(), (size_t)nt);
+  up.add(ts.order.p, order.data(), (size_t)nt);
   ts.tl.order = ts.order.p;
 }
 
@@ -969,7 +1012,7 @@ CellPlan cell_plan(const rp_system* s, int cus, size_t width, int64_t most) {
 // those of the shortest modelled sweep: fewer rows even out the blocks' lists,
 // more rows stage fewer panels.
 void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBuf<int32_t>& blk,
-                      const rp_system::TileSet& main, size_t width) {
+                      const rp_system::TileSet& main, size_t width, Uploads& up) {
   const int K = s->K;
   ts.ok = false;
   if (s->npad <= 0 || !main.ok || ctx->cus < 8) return;
@@ -1008,7 +1051,7 @@ void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBu
   tc0[K] = (int32_t)trow0.size();
   const int32_t nt = tc0[K];
   dalloc(ctx, blk, plan.first.size());
-  to_dev(ctx, blk.p, plan.first.data(), plan.first.size());
+  up.add(blk.p, plan.first.data(), plan.first.size());
   dalloc(ctx, ts.row0, (size_t)nt);
   dalloc(ctx, ts.nrows, (size_t)nt);
   dalloc(ctx, ts.inst, (size_t)nt);
@@ -1017,14 +1060,14 @@ void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBu
   dalloc(ctx, ts.nw, (size_t)nt);
   dalloc(ctx, ts.kind, (size_t)nt);
   dalloc(ctx, ts.order, (size_t)nt);
-  to_dev(ctx, ts.row0.p, trow0.data(), (size_t)nt);
-  to_dev(ctx, ts.nrows.p, tnr.data(), (size_t)nt);
-  to_dev(ctx, ts.inst.p, tinst.data(), (size_t)nt);
-  to_dev(ctx, ts.inst0.p, tc0.data(), (size_t)K + 1);
-  to_dev(ctx, ts.w0.p, tw0.data(), (size_t)nt);
-  to_dev(ctx, ts.nw.p, tnw.data(), (size_t)nt);
-  to_dev(ctx, ts.kind.p, tkind.data(), (size_t)nt);
-  to_dev(ctx, ts.order.p, plan.order.data(), (size_t)nt);
+  up.add(ts.row0.p, trow0.data(), (size_t)nt);
+  up.add(ts.nrows.p, tnr.data(), (size_t)nt);
+  up.add(ts.inst.p, tinst.data(), (size_t)nt);
+  up.add(ts.inst0.p, tc0.data(), (size_t)K + 1);
+  up.add(ts.w0.p, tw0.data(), (size_t)nt);
+  up.add(ts.nw.p, tnw.data(), (size_t)nt);
+  up.add(ts.kind.p, tkind.data(), (size_t)nt);
+  up.add(ts.order.p, plan.order.data(), (size_t)nt);
   ts.kind_h = tkind;
   ts.inst0_h = tc0;
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, 0};
@@ -1037,7 +1080,7 @@ void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBu
 // kResidentBytes.
 constexpr double kResidentBytes = 512.0 * 1024.0;
 
-void build_resident(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t width) {
+void build_resident(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_t width, Uploads& up) {
   const int K = s->K;
   ts.ok = false;
   if (s->npad <= 0) return;
@@ -1071,13 +1114,13 @@ void build_resident(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_
   dalloc(ctx, ts.w0, (size_t)nt);
   dalloc(ctx, ts.nw, (size_t)nt);
   dalloc(ctx, ts.kind, (size_t)nt);
-  to_dev(ctx, ts.row0.p, trow0.data(), (size_t)nt);
-  to_dev(ctx, ts.nrows.p, tnr.data(), (size_t)nt);
-  to_dev(ctx, ts.inst.p, tinst.data(), (size_t)nt);
-  to_dev(ctx, ts.inst0.p, tc0.data(), (size_t)K + 1);
-  to_dev(ctx, ts.w0.p, tw0.data(), (size_t)nt);
-  to_dev(ctx, ts.nw.p, tnw.data(), (size_t)nt);
-  to_dev(ctx, ts.kind.p, tkind.data(), (size_t)nt);
+  up.add(ts.row0.p, trow0.data(), (size_t)nt);
+  up.add(ts.nrows.p, tnr.data(), (size_t)nt);
+  up.add(ts.inst.p, tinst.data(), (size_t)nt);
+  up.add(ts.inst0.p, tc0.data(), (size_t)K + 1);
+  up.add(ts.w0.p, tw0.data(), (size_t)nt);
+  up.add(ts.nw.p, tnw.data(), (size_t)nt);
+  up.add(ts.kind.p, tkind.data(), (size_t)nt);
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, (int32_t)maxw};
   ts.ok = true;
 }
@@ -1096,6 +1139,7 @@ constexpr int kTailInstances = 16;
 
 bool build_tail(rp_context* ctx, rp_system* s, size_t width, const std::vector<int32_t>& status_h,
                 const rp_system::TileSet& main, const std::vector<int32_t>* t_s0_h) {
+  Uploads up(ctx);
   const int K = s->K;
   const double w = (double)width;
   std::vector<int32_t> trow0, tnr, tinst, tkind, tc0(K + 1, 0);
@@ -1126,8 +1170,8 @@ bool build_tail(rp_context* ctx, rp_system* s, size_t width, const std::vector<i
   if (sliced) {
     dalloc(ctx, s->tail_slo, (size_t)nt);
     dalloc(ctx, s->tail_shi, (size_t)nt);
-    to_dev(ctx, s->tail_slo.p, slo.data(), (size_t)nt);
-    to_dev(ctx, s->tail_shi.p, shi.data(), (size_t)nt);
+    up.add(s->tail_slo.p, slo.data(), (size_t)nt);
+    up.add(s->tail_shi.p, shi.data(), (size_t)nt);
   }
   s->tail_sliced = sliced;
   rp_system::TileSet& ts = s->tail;
@@ -1136,13 +1180,14 @@ bool build_tail(rp_context* ctx, rp_system* s, size_t width, const std::vector<i
   dalloc(ctx, ts.inst, (size_t)nt);
   dalloc(ctx, ts.inst0, (size_t)K + 1);
   dalloc(ctx, ts.kind, (size_t)nt);
-  to_dev(ctx, ts.row0.p, trow0.data(), (size_t)nt);
-  to_dev(ctx, ts.nrows.p, tnr.data(), (size_t)nt);
-  to_dev(ctx, ts.inst.p, tinst.data(), (size_t)nt);
-  to_dev(ctx, ts.inst0.p, tc0.data(), (size_t)K + 1);
-  to_dev(ctx, ts.kind.p, tkind.data(), (size_t)nt);
+  up.add(ts.row0.p, trow0.data(), (size_t)nt);
+  up.add(ts.nrows.p, tnr.data(), (size_t)nt);
+  up.add(ts.inst.p, tinst.data(), (size_t)nt);
+  up.add(ts.inst0.p, tc0.data(), (size_t)K + 1);
+  up.add(ts.kind.p, tkind.data(), (size_t)nt);
   // the window of a resident tile is its instance block: w0 = row0, nw = nrows
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.row0.p, ts.nrows.p, ts.kind.p, nt, K, (int32_t)maxw};
+  up.run();
   ts.ok = true;
   return true;
 }
@@ -1263,6 +1308,7 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   }
   if (tr) ensure_transpose(ctx, s);
   hipStream_t st = ctx->stream;
+  Uploads up(ctx);
   const Tiles& tl = ts.tl;
   const int32_t nt = tl.ntile;
   std::vector<int32_t> t_s0(nt + 1, 0), stile;
@@ -1275,18 +1321,20 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   dalloc(ctx, ss.t_s0, (size_t)nt + 1);
   dalloc(ctx, ss.row, (size_t)nslice * SLICE);
   dalloc(ctx, ss.width, (size_t)nslice);
-  to_dev(ctx, ss.t_s0.p, t_s0.data(), (size_t)nt + 1);
+  up.add(ss.t_s0.p, t_s0.data(), (size_t)nt + 1);
   MatView<T> m = view<T>(s, tr);
+  up.run();
   HIPCHK(ctx, launch_slice_order(st, m.rp, tl, ss.t_s0.p, sort_window(s), ss.row.p, ss.width.p));
   bool any_band = false;
   for (int32_t t = 0; t < nt; t++) any_band = any_band || ts.kind_h[t] == WIN_BAND;
   DBuf<int32_t> stile_d, nfar_d, far0_d, inexact;
   dalloc(ctx, stile_d, (size_t)nslice);
-  to_dev(ctx, stile_d.p, stile.data(), (size_t)nslice);
+  up.add(stile_d.p, stile.data(), (size_t)nslice);
   dalloc(ctx, nfar_d, (size_t)nslice);
   dalloc(ctx, far0_d, (size_t)nslice);
   std::vector<int32_t> width(nslice), nfar(nslice, 0), far0(nslice, 0);
   if (any_band) {
+    up.run();
     HIPCHK(ctx, launch_slice_far(st, m.rp, m.col, tl, stile_d.p, nslice, ss.row.p, nfar_d.p));
     to_host(ctx, nfar.data(), nfar_d.p, (size_t)nslice);
   }
@@ -1361,15 +1409,15 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
     dalloc(ctx, ss.hoff, (size_t)nt);
     dalloc(ctx, ss.pend, (size_t)nt);
     dalloc(ctx, ss.cnt, (size_t)ncnt);
-    to_dev(ctx, ss.npan.p, npan.data(), (size_t)nt);
-    to_dev(ctx, ss.hoff.p, hoff.data(), (size_t)nt);
-    to_dev(ctx, ss.pend.p, pend.data(), (size_t)nt);
+    up.add(ss.npan.p, npan.data(), (size_t)nt);
+    up.add(ss.hoff.p, hoff.data(), (size_t)nt);
+    up.add(ss.pend.p, pend.data(), (size_t)nt);
     DBuf<int32_t> ent_d;
     dalloc(ctx, ps_d, (size_t)nps);
     dalloc(ctx, pt_d, (size_t)nps);
     dalloc(ctx, ent_d, (size_t)nps);
-    to_dev(ctx, ps_d.p, pslice.data(), (size_t)nps);
-    to_dev(ctx, pt_d.p, ptile.data(), (size_t)nps);
+    up.add(ps_d.p, pslice.data(), (size_t)nps);
+    up.add(pt_d.p, ptile.data(), (size_t)nps);
     Sliced<T> pv{};
     pv.t_s0 = ss.t_s0.p;
     pv.row = ss.row.p;
@@ -1377,6 +1425,7 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
     pv.hoff = ss.hoff.p;
     pv.pend = ss.pend.p;
     pv.pw = (int32_t)pw;
+    up.run();
     HIPCHK(ctx, launch_panel_count<T>(st, m, tl, pv, ps_d.p, pt_d.p, nps, ss.cnt.p, ent_d.p));
     std::vector<int32_t> ent((size_t)nps);
     to_host(ctx, ent.data(), ent_d.p, (size_t)nps);
@@ -1387,8 +1436,8 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
     }
     if (total + pent + PANEL_SLACK > INT32_MAX) return false;
     dalloc(ctx, ss.pent, (size_t)nslice);
-    to_dev(ctx, ss.pent.p, pstart.data(), (size_t)nslice);
-    to_dev(ctx, ss.width.p, width.data(), (size_t)nslice);  // paneled slices: no regular slots
+    up.add(ss.pent.p, pstart.data(), (size_t)nslice);
+    up.add(ss.width.p, width.data(), (size_t)nslice);  // paneled slices: no regular slots
   }
   // slots: regular (nslot), of paneled slices, then zeros (SLICE, PANEL_SLACK)
   const int64_t nent = total + pent + std::max(SLICE, PANEL_SLACK);
@@ -1411,10 +1460,10 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   else dalloc(ctx, ss.val, (size_t)nent);
   if (any16 || npaneled > 0) dalloc(ctx, ss.c16, (size_t)nent);
   if (any32) dalloc(ctx, ss.c32, (size_t)nent);
-  to_dev(ctx, ss.off.p, off.data(), (size_t)nslice);
-  to_dev(ctx, ss.wide.p, wide.data(), (size_t)nt);
-  to_dev(ctx, nfar_d.p, nfar.data(), (size_t)nslice);
-  to_dev(ctx, far0_d.p, far0.data(), (size_t)nslice);
+  up.add(ss.off.p, off.data(), (size_t)nslice);
+  up.add(ss.wide.p, wide.data(), (size_t)nt);
+  up.add(nfar_d.p, nfar.data(), (size_t)nslice);
+  up.add(far0_d.p, far0.data(), (size_t)nslice);
   ss.v = Sliced<T>{};
   ss.v.t_s0 = ss.t_s0.p;
   ss.v.off = ss.off.p;
@@ -1433,6 +1482,7 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   ss.v.nslot = (int32_t)(total + pent);
   ss.v.narrow = total < (int64_t)kNarrowSlots * SLICE * nslice ? 1 : 0;
   HIPCHK(ctx, launch_set_i32(st, ss.far.p, 0));  // read where a slice has none
+  up.run();
   HIPCHK(ctx, launch_slice_fill<T>(st, m, tl, stile_d.p, ss.v, far0_d.p, nfar_d.p));
   // Slices larger than the last-level cache are read with nontemporal loads:
   // they cannot stay cached from one sweep to the next anyway, and streaming
@@ -2513,6 +2563,7 @@ void partition_searches(rp_context* ctx, const rp_chain* chain, const uint8_t* g
 // the chunk and tile layouts.  Shared by rp_precompute and rp_matrix_system.
 void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32_t* flags_sq_p) {
   hipStream_t st = ctx->stream;
+  Uploads up(ctx);
   const int64_t n = chain->n, nnz = chain->nnz;
   const int32_t K = chain->num_instances;
   DBuf<int32_t> rank, scan_tmp;
@@ -2534,9 +2585,10 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   }
   s->npad = s->roff_h[K];
   dalloc(ctx, s->roff, (size_t)K + 1);
-  to_dev(ctx, s->roff.p, s->roff_h.data(), (size_t)K + 1);
+  up.add(s->roff.p, s->roff_h.data(), (size_t)K + 1);
   dalloc(ctx, s->nq, (size_t)K);
-  to_dev(ctx, s->nq.p, s->nq_h.data(), (size_t)K);
+  up.add(s->nq.p, s->nq_h.data(), (size_t)K);
+  up.run();
 
   const int64_t np = s->npad;
   dalloc(ctx, s->map, (size_t)n);
@@ -2557,10 +2609,9 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   dalloc(ctx, scratch2, scan_scratch_elems(np));
   HIPCHK(ctx, launch_scan(st, rcnt.p, s->fwd.rp.p, np, scratch2.p));
   int32_t z = 0;
-  to_host(ctx, &z, s->fwd.rp.p + np, 1);
-  s->z = z;
   {
-    // off-diagonal entries per instance (row pointers at the block starts)
+    // off-diagonal entries per instance and in all (row pointers at the block
+    // starts; the last one is at npad)
     DBuf<int32_t> at;
     dalloc(ctx, at, (size_t)K + 1);
     HIPCHK(ctx, launch_gather_at(st, s->fwd.rp.p, s->roff.p, K + 1, at.p));
@@ -2568,6 +2619,7 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
     to_host(ctx, ath.data(), at.p, (size_t)K + 1);
     s->z_h.resize(K);
     for (int k = 0; k < K; k++) s->z_h[k] = ath[k + 1] - ath[k];
+    s->z = z = ath[K];
   }
   dalloc(ctx, s->fwd.col, (size_t)z + 1);
   dalloc(ctx, s->fwd.v64, (size_t)z + 1);
@@ -2604,10 +2656,11 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   dalloc(ctx, s->c_nrows, (size_t)nchunk);
   dalloc(ctx, s->c_inst, (size_t)nchunk);
   dalloc(ctx, s->c_inst0, (size_t)K + 1);
-  to_dev(ctx, s->c_row0.p, row0.data(), (size_t)nchunk);
-  to_dev(ctx, s->c_nrows.p, nrows.data(), (size_t)nchunk);
-  to_dev(ctx, s->c_inst.p, cinst.data(), (size_t)nchunk);
-  to_dev(ctx, s->c_inst0.p, c0.data(), (size_t)K + 1);
+  up.add(s->c_row0.p, row0.data(), (size_t)nchunk);
+  up.add(s->c_nrows.p, nrows.data(), (size_t)nchunk);
+  up.add(s->c_inst.p, cinst.data(), (size_t)nchunk);
+  up.add(s->c_inst0.p, c0.data(), (size_t)K + 1);
+  up.run();
   s->chunk_inst_h = cinst;
   s->chunk_c0_h = c0;
   s->ch = Chunks{s->c_row0.p, s->c_nrows.p, s->c_inst.p, s->c_inst0.p, nchunk, K};
@@ -2627,14 +2680,15 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
     hist.resize((size_t)K * 32);
     to_host(ctx, hist.data(), dh.p, (size_t)K * 32);
   }
-  build_tiles(ctx, s, s->t64, sizeof(double), 1, hist);
-  build_tiles(ctx, s, s->t32, sizeof(float), 2, hist);
-  build_resident(ctx, s, s->res64, sizeof(double));
-  build_resident(ctx, s, s->res32, sizeof(float));
-  build_cell_tiles(ctx, s, s->c64, s->cblk64, s->t64, sizeof(double));
-  build_cell_tiles(ctx, s, s->c32, s->cblk32, s->t32, sizeof(float));
+  build_tiles(ctx, s, s->t64, sizeof(double), 1, hist, up);
+  build_tiles(ctx, s, s->t32, sizeof(float), 2, hist, up);
+  build_resident(ctx, s, s->res64, sizeof(double), up);
+  build_resident(ctx, s, s->res32, sizeof(float), up);
+  build_cell_tiles(ctx, s, s->c64, s->cblk64, s->t64, sizeof(double), up);
+  build_cell_tiles(ctx, s, s->c32, s->cblk32, s->t32, sizeof(float), up);
   for (const rp_system::TileSet* t : {&s->t64, &s->t32, &s->c64, &s->c32})
     if (t->ok) s->ntile_max = std::max(s->ntile_max, t->tl.ntile);
+  up.run();
   HIPCHK(ctx, hipStreamSynchronize(st));
 }
 
@@ -3034,12 +3088,13 @@ int rp_precompute(rp_context* ctx, const rp_chain* chain, const uint8_t* goal_ma
     s->nnz = nnz;
     s->inst_off_h.assign(off, off + K + 1);
     dalloc(ctx, s->inst_off, (size_t)K + 1);
-    to_dev(ctx, s->inst_off.p, off, (size_t)K + 1);
+    Uploads up(ctx);
+    up.add(s->inst_off.p, off, (size_t)K + 1);
+    up.run();
 
     // -- validation (Section 2: a row-stochastic transition function)
     int32_t ends[2];
-    to_host(ctx, &ends[0], chain->row_ptr, 1);
-    to_host(ctx, &ends[1], chain->row_ptr + n, 1);
+    HostReads(ctx).add(&ends[0], chain->row_ptr, 1).add(&ends[1], chain->row_ptr + n, 1).run();
     if (ends[0] != 0 || ends[1] != nnz) {
       set_err(ctx, "row %lld: %s (row_ptr[0] = %d, row_ptr[n] = %d, nnz = %lld)", (long long)n, reason_text(1),
               ends[0], ends[1], (long long)nnz);
@@ -3134,10 +3189,11 @@ int rp_matrix_system(rp_context* ctx, int32_t num_instances, const int64_t* inst
     s->general = true;
     s->inst_off_h.assign(off, off + K + 1);
     dalloc(ctx, s->inst_off, (size_t)K + 1);
-    to_dev(ctx, s->inst_off.p, off, (size_t)K + 1);
+    Uploads up(ctx);
+    up.add(s->inst_off.p, off, (size_t)K + 1);
+    up.run();
     int32_t ends[2];
-    to_host(ctx, &ends[0], row_ptr, 1);
-    to_host(ctx, &ends[1], row_ptr + n, 1);
+    HostReads(ctx).add(&ends[0], row_ptr, 1).add(&ends[1], row_ptr + n, 1).run();
     if (ends[0] != 0 || ends[1] != nnz) {
       set_err(ctx, "row %lld: %s (row_ptr[0] = %d, row_ptr[n] = %d, nnz = %lld)", (long long)n, reason_text(1),
               ends[0], ends[1], (long long)nnz);

@@ -464,6 +464,15 @@ hipError_t launch_gradient(hipStream_t st, int64_t n, const int32_t* rp, const i
                            const double* xfull, double* g);
 hipError_t launch_fill_f64(hipStream_t st, double* p, int64_t n, double v);
 hipError_t launch_fill_u32(hipStream_t st, uint32_t* p, int64_t n, uint32_t v);
+// Several small host arrays to their device arrays with one launch: part i is
+// `bytes` (a multiple of 4) from src + off, src pinned host memory as the device
+// sees it and 16-byte aligned offsets.
+constexpr int UPLOAD_PARTS = 64;
+struct UploadTable {
+  void* dst[UPLOAD_PARTS];
+  uint32_t off[UPLOAD_PARTS], bytes[UPLOAD_PARTS];
+};
+hipError_t launch_upload(hipStream_t st, const unsigned char* src, const UploadTable& t, int parts);
 hipError_t launch_publish(hipStream_t st, const int32_t* src, int32_t* dst, int32_t seq);
 hipError_t launch_col16(hipStream_t st, Chunks ch, const int64_t* roff, const int32_t* rp, const int32_t* col,
                         uint16_t* c16);

@@ -4668,6 +4668,30 @@ hipError_t launch_set_i32(hipStream_t st, int32_t* p, int32_t v) {
   return hipGetLastError();
 }
 
+// blockIdx.x: part, blockIdx.y: every UPLOAD_SPLIT-th run of it.  Bound by the
+// link's latency: a part of up to 64 KB is read with two loads per thread.
+constexpr int UPLOAD_SPLIT = 8;
+__global__ __launch_bounds__(BS) void k_upload(const unsigned char* __restrict__ src, UploadTable t) {
+  const int i = blockIdx.x;
+  const uint32_t* __restrict__ in = reinterpret_cast<const uint32_t*>(src + t.off[i]);
+  uint32_t* __restrict__ out = static_cast<uint32_t*>(t.dst[i]);
+  const uint32_t n = t.bytes[i] / 4, q = n / 4;
+  for (uint32_t k = blockIdx.y * BS + threadIdx.x; k < q; k += BS * UPLOAD_SPLIT) {
+    const uint4 v = reinterpret_cast<const uint4*>(in)[k];
+    out[4 * k] = v.x;
+    out[4 * k + 1] = v.y;
+    out[4 * k + 2] = v.z;
+    out[4 * k + 3] = v.w;
+  }
+  if (blockIdx.y == 0 && threadIdx.x < n - 4 * q) out[4 * q + threadIdx.x] = in[4 * q + threadIdx.x];
+}
+hipError_t launch_upload(hipStream_t st, const unsigned char* src, const UploadTable& t, int parts) {
+  if (parts <= 0) return hipSuccess;
+  if (parts > UPLOAD_PARTS) return hipErrorInvalidValue;
+  k_upload<<<dim3((unsigned)parts, UPLOAD_SPLIT), BS, 0, st>>>(src, t);
+  return hipGetLastError();
+}
+
 __global__ void k_publish(const int32_t* __restrict__ src, int32_t* dst, int32_t seq) {
   if (threadIdx.x == 0) {
     dst[0] = *src;
