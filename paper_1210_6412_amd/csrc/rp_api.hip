@@ -2503,12 +2503,18 @@ void solve_core(rp_context* ctx, rp_system* s, bool tr, int method, const double
 // Pull-step batches of a search before its states of equal reachability are
 // merged (a search that has not settled by then is a deep one).
 constexpr int kPlainBatches = 4;
+// A workgroup's pass over 20,000 states takes some 40 us, a pull step over the
+// GPU 3.6: a search of them 315 us -> 59 (of which the workgroup's last pass 30).
+// Below 4,000 states a pass costs what two launches do.
+constexpr int64_t kReachSpread = 4096;
+constexpr int32_t kReachFirst = 8;
 
 // The two backward searches of Section 2.2 (the second never passes a goal
 // state), into reach_goal and, unless prob0_only, reach_s0 (n marks each);
 // changed is one device word (the number of the last pull step that marked a
-// state).  Chains of at most REACH_RESIDENT_MAX states run the whole search
-// in one workgroup, larger ones in pull steps, batches of 8 launches per host
+// state).  Chains of at most REACH_RESIDENT_MAX states run the search in one
+// workgroup (from kReachSpread states on after kReachFirst pull steps over the
+// whole GPU), larger ones in pull steps, batches of 8 launches per host
 // check (the steps after the fixed point return at once).  With parent and cmark (n words each, or
 // null), a search still running after kPlainBatches batches merges the
 // states of equal reachability (launch_reach_contract) and continues on the
@@ -2520,6 +2526,11 @@ void partition_searches(rp_context* ctx, const rp_chain* chain, const uint8_t* g
   const int64_t n = chain->n;
   auto search = [&](uint32_t* mark, const uint8_t* blocked) {
     if (n <= REACH_RESIDENT_MAX) {
+      if (n >= kReachSpread) {
+        HIPCHK(ctx, launch_fill_u32(st, reinterpret_cast<uint32_t*>(changed), 1, 0u));
+        for (int32_t step = 1; step <= kReachFirst; step++)
+          HIPCHK(ctx, launch_reach_step(st, n, chain->row_ptr, chain->col, chain->val, blocked, mark, changed, step));
+      }
       HIPCHK(ctx, launch_reach_resident(st, n, chain->row_ptr, chain->col, chain->val, blocked, mark));
       return;
     }

