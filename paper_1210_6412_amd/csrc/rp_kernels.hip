@@ -1443,6 +1443,59 @@ template hipError_t launch_jacobi_tile<float>(hipStream_t, int, MatView<float>, 
                                               Tiles, int64_t, const double*, double*, int32_t*, int64_t*, double*,
                                               const double*, int, int64_t, int32_t*, int);
 
+// Maximum over the block of a value that is not negative (or NaN, which wins) in
+// every thread; one barrier, which also orders the LDS writes before it against
+// the reads after it.  red: TNT/64 slots, others than in the call before.
+__device__ __forceinline__ double resident_max(double v, unsigned long long* red) {
+  // the bits of such values order as integers do
+  unsigned long long a = (unsigned long long)__double_as_longlong(v) & 0x7FFFFFFFFFFFFFFFull;
+  auto step = [&](auto dpp) {
+    const unsigned lo = (unsigned)dpp((int)(unsigned)a), hi = (unsigned)dpp((int)(a >> 32));
+    const unsigned long long b = ((unsigned long long)hi << 32) | lo;
+    a = b > a ? b : a;
+  };
+  auto row16 = [&]() {  // rotations by 8, 4, 2, 1 within the 16 lanes of a row
+    step([](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false); });
+    step([](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x124, 0xF, 0xF, false); });
+    step([](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x122, 0xF, 0xF, false); });
+    step([](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x121, 0xF, 0xF, false); });
+  };
+  row16();
+  step([](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x142, 0xA, 0xF, false); });  // lane 15 to the next row
+  step([](int x) { return __builtin_amdgcn_update_dpp(x, x, 0x143, 0xC, 0xF, false); });  // lane 31 to the rows above
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = a;
+  __syncthreads();
+  static_assert(TNT / 64 == 16, "a value per lane of a row");
+  a = red[threadIdx.x & 15];
+  row16();
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The decision after a resident sweep (done sweeps completed), the same in every
+// thread: the instance's state, and whether the launch ends with this sweep.
+struct ResidentStop {
+  double th;
+  int32_t st;
+  __device__ __forceinline__ bool stop(double mm, int inst, int64_t done, bool last, int32_t* status, int64_t* iters,
+                                       double* meas, int strict, int64_t max_iter, int32_t* ndone) {
+    st = ST_RUN;
+    if (!finite(mm)) st = ST_NONFINITE;
+    else if (strict ? (mm < th) : (mm <= th)) st = ST_CONVERGED;
+    else if (done >= max_iter) st = ST_MAXITER;
+    if (st == ST_RUN && !last) return false;
+    if (threadIdx.x == 0) {
+      meas[inst] = mm;
+      if (st != ST_RUN) {
+        status[inst] = st;
+        iters[inst] = done;
+        atomicAdd(ndone, 1);
+      }
+    }
+    return true;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Resident Jacobi: one block holds a whole small instance -- both iterates in
 // LDS -- and runs up to nsweeps sweeps in one launch, deciding after each one
@@ -1451,6 +1504,12 @@ template hipError_t launch_jacobi_tile<float>(hipStream_t, int, MatView<float>, 
 // On exit the latest iterate goes to the buffer the sweep-count parity
 // names (xb when odd), like the tiled sweeps leave it.  When the instance's
 // rows fit one row batch the matrix rows stay in registers across sweeps.
+// A sweep is a chain of latencies (LDS reads, the sum, the division where d is not
+// 1, the maximum, the barrier); nothing else may wait in it: the threshold is read
+// once, the measure written when the launch ends, the maximum taken by lane
+// permutes within the vector unit and one barrier.  1,000 states of a gambler's
+// ruin: 1.5 -> 1.0 us per FP64 sweep (four barriers, and a global load and store
+// before two of them).
 template <typename T, int L>
 __device__ __forceinline__ double resident_rows(const RowBatch<T, L>& rb, const MatView<T>& m, const T* __restrict__ cur,
                                                 T* __restrict__ nxt, int base, int nr, int lane, int weighted) {
@@ -1462,7 +1521,8 @@ __device__ __forceinline__ double resident_rows(const RowBatch<T, L>& rb, const 
     const T acc = rb.template sum<WIN_WHOLE>(m, cur, nullptr, 0, u, lane, 0);
     const int i = base + u * RPP + g;
     if (i < nr && lane == 0) {
-      const T nv = (rb.bi[u] + acc) / rb.di[u];
+      const T t = rb.bi[u] + acc;
+      const T nv = __ballot(rb.di[u] != (T)1) ? t / rb.di[u] : t;
       const double dl = fabs((double)nv - (double)cur[i]);
       nxt[i] = nv;
       mloc = mx(mloc, weighted ? (double)rb.di[u] * dl : dl);
@@ -1478,10 +1538,11 @@ __global__ __launch_bounds__(TNT) void k_jacobi_resident(MatView<T> m, const T* 
                                                          const double* __restrict__ thr, int strict,
                                                          int64_t max_iter, int32_t* ndone, int weighted) {
   extern __shared__ unsigned char smem_raw[];
-  __shared__ int32_t decision;
+  __shared__ unsigned long long red[2][TNT / 64];
   const int c = blockIdx.x;
   const int inst = tl.inst[c];
   if (status[inst] != ST_RUN) return;
+  ResidentStop end{thr[inst], ST_RUN};
   const int r0 = tl.row0[c], nr = tl.nrows[c];  // the tile is the whole instance block (w0 = r0, nw = nr)
   T* X0 = reinterpret_cast<T*>(smem_raw);
   T* X1 = X0 + tl.maxw;
@@ -1505,30 +1566,14 @@ __global__ __launch_bounds__(TNT) void k_jacobi_resident(MatView<T> m, const T* 
         mloc = mx(mloc, resident_rows<T, L>(rbi, m, cur, nxt, base, nr, lane, weighted));
       }
     }
-    double v[1] = {mloc};
-    block_reduce<1, TNT>(v, 1u);
+    const double mm = resident_max(mloc, red[it & 1]);
     const int64_t done = s0 + it + 1;  // sweeps completed
-    if (threadIdx.x == 0) {
-      const double mm = v[0];
-      int32_t st = ST_RUN;
-      if (!finite(mm)) st = ST_NONFINITE;
-      else if (strict ? (mm < thr[inst]) : (mm <= thr[inst])) st = ST_CONVERGED;
-      else if (done >= max_iter) st = ST_MAXITER;
-      meas[inst] = mm;
-      if (st != ST_RUN) {
-        status[inst] = st;
-        iters[inst] = done;
-        atomicAdd(ndone, 1);
-      }
-      decision = st;
-    }
-    __syncthreads();
-    if (decision != ST_RUN || it == nsweeps - 1) {
+    if (end.stop(mm, inst, done, it == nsweeps - 1, status, iters, meas, strict, max_iter, ndone)) {
       T* dst = (done & 1) ? xb : xa;
       for (int i = threadIdx.x; i < nr; i += TNT) dst[r0 + i] = nxt[i];
       // a weighted measure is the residual of the previous iterate: keep it
       // in the other buffer, as the tiled sweeps do
-      if (decision != ST_RUN && weighted) {
+      if (end.st != ST_RUN && weighted) {
         T* dprev = (done & 1) ? xa : xb;
         for (int i = threadIdx.x; i < nr; i += TNT) dprev[r0 + i] = cur[i];
       }
@@ -3175,10 +3220,11 @@ __global__ __launch_bounds__(TNT) void k_jacobi_resident_sliced(Sliced<T> sl, co
                                                                 int strict, int64_t max_iter, int32_t* ndone,
                                                                 int weighted) {
   extern __shared__ unsigned char smem_raw[];
-  __shared__ int32_t decision;
+  __shared__ unsigned long long red[2][TNT / 64];
   const int c = blockIdx.x;
   const int inst = tl.inst[c];
   if (status[inst] != ST_RUN) return;
+  ResidentStop end{thr[inst], ST_RUN};
   const int r0 = tl.row0[c], nr = tl.nrows[c];  // the instance block
   const int sb = s_lo[c], se = s_hi[c];
   T* X0 = reinterpret_cast<T*>(smem_raw);
@@ -3188,30 +3234,14 @@ __global__ __launch_bounds__(TNT) void k_jacobi_resident_sliced(Sliced<T> sl, co
   for (int it = 0; it < nsweeps; it++) {
     const T* cur = (it & 1) ? X1 : X0;
     T* nxt = (it & 1) ? X0 : X1;
-    double v[1] = {resident_sliced_rows<T, VT>(sl, rhs, cur, nxt, sb, se, r0, weighted)};
-    block_reduce<1, TNT>(v, 1u);
+    const double mm = resident_max(resident_sliced_rows<T, VT>(sl, rhs, cur, nxt, sb, se, r0, weighted), red[it & 1]);
     const int64_t done = s0 + it + 1;  // sweeps completed
-    if (threadIdx.x == 0) {
-      const double mm = v[0];
-      int32_t st = ST_RUN;
-      if (!finite(mm)) st = ST_NONFINITE;
-      else if (strict ? (mm < thr[inst]) : (mm <= thr[inst])) st = ST_CONVERGED;
-      else if (done >= max_iter) st = ST_MAXITER;
-      meas[inst] = mm;
-      if (st != ST_RUN) {
-        status[inst] = st;
-        iters[inst] = done;
-        atomicAdd(ndone, 1);
-      }
-      decision = st;
-    }
-    __syncthreads();
-    if (decision != ST_RUN || it == nsweeps - 1) {
+    if (end.stop(mm, inst, done, it == nsweeps - 1, status, iters, meas, strict, max_iter, ndone)) {
       T* dst = (done & 1) ? xb : xa;
       for (int i = threadIdx.x; i < nr; i += TNT) dst[r0 + i] = nxt[i];
       // a weighted measure is the residual of the previous iterate: keep it
       // in the other buffer, as the tiled sweeps do
-      if (decision != ST_RUN && weighted) {
+      if (end.st != ST_RUN && weighted) {
         T* dprev = (done & 1) ? xa : xb;
         for (int i = threadIdx.x; i < nr; i += TNT) dprev[r0 + i] = cur[i];
       }
