@@ -51,7 +51,7 @@ def pmc_traffic(kernel_id, kernel_name=None, workload=None):
     and WRITE_SIZE runs (scaled by a plain copy of known size), or None when
     the kernel sources changed since the counters were taken, the counters
     were taken on another workload, or they are of another kernel than
-    kernel_name (a name or name prefix: another row layout)."""
+    kernel_name (a name, name prefix or prefixes: another row layout)."""
     try:
         with open(PMC_FILE) as f:
             d = json.load(f)
@@ -506,7 +506,7 @@ def main():
     out_extra = {}
     if not args.no_extras:
         out_extra = extras(args, chain, ctx, rows, step, times, seed_v, dev, rp, B, x, rowp, col, val, goal, off, cls)
-    roof, kernels = roofline(prof, {k: v[0]["lanes"] for k, v in last.items()}, chain.name)
+    roof, kernels = roofline(prof, {k: v[0]["lanes"] for k, v in last.items()}, chain.name, args.schedule)
 
     out = {
         "metric": METRIC, "value": round(value, 3), "unit": "solves/s", "n_gpus": 1, "steps": args.steps,
@@ -533,16 +533,20 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-def sweep_kernel(kernel_id, lanes):
-    """Name (prefix) of the Jacobi sweep kernel a solve ran, from its reported
-    layout (0: sliced rows, L > 0: L lanes per row), as the profilers print it."""
+def sweep_kernel(kernel_id, lanes, schedule=-1):
+    """Name (prefix, or prefixes) of the Jacobi sweep kernel a solve ran, from its
+    reported layout (0: cells or, always with schedule 0, sliced rows; L > 0: L
+    lanes per row), as the profilers print it."""
     t = {"jacobi_fp64": "double", "jacobi_fp32": "float"}.get(kernel_id)
     if t is None or lanes is None:
         return None
-    return f"rpk::k_jacobi_sliced<{t}," if lanes == 0 else f"rpk::k_jacobi_tile<{t}, {lanes}>"
+    if lanes != 0:
+        return f"rpk::k_jacobi_tile<{t}, {lanes}>"
+    sliced = f"rpk::k_jacobi_sliced<{t},"
+    return sliced if schedule == 0 else (f"rpk::k_jacobi_cells<{t}>", sliced)
 
 
-def roofline(prof, layouts=None, workload=None):
+def roofline(prof, layouts=None, workload=None, schedule=-1):
     """Roofline entry for the kernel with the most time, from the library's
     event timing: algorithmic bytes / summed time over the timed steps.
     layouts: lanes reported per solve row (selects the kernel whose byte
@@ -560,7 +564,7 @@ def roofline(prof, layouts=None, workload=None):
     roof = {"bound": "hbm", "kernel": dom, "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4),
             "traffic": pmc_traffic(dom, sweep_kernel(dom, (layouts or {}).get(
-                {"jacobi_fp64": "jacobi_fp64", "jacobi_fp32": "jacobi_fp32r"}.get(dom, dom))), workload),
+                {"jacobi_fp64": "jacobi_fp64", "jacobi_fp32": "jacobi_fp32r"}.get(dom, dom)), schedule), workload),
             "launches": n, "avg_launch_us": round(1000 * ms / n, 3), "alg_bytes_per_launch": b / n}
     return roof, kernels
 

@@ -2925,8 +2925,9 @@ __device__ __forceinline__ const VT* slice_values(const Sliced<T>& sl) {
 // wait for all loads).  Fewer bytes come second: 16-bit rows and columns, no
 // diagonal where it is 1, FP64 values that FP32 holds exactly in 4 bytes; far
 // entries' x are gathered by one load per slice, a lane each, and handed to
-// their rows with a lane permute.  us per sweep, before (row numbers, then rhs; scalar widths,
-// then entries; 4-byte row numbers and band columns; every diagonal) -> now:
+// their rows with a lane permute.  us per sweep, before (row numbers, then rhs;
+// scalar widths, then entries; 4-byte row numbers and band columns; every
+// diagonal) -> now:
 // 33.5 M-state program graph FP64 608 -> 451 (4.1 TB/s of what is now read), FP32
 // 426 -> 350; 2 M states 29.7 -> 22.9, 21.7 -> 18.9; 500 chains of 16,000 137 ->
 // 127, 77 -> 72.6; 64 chains of 20,000 29.2 -> 28.0, 19.0 -> 18.3.  Fewer bytes
