@@ -1288,8 +1288,17 @@ int32_t sort_window(const rp_system* s) {
 }
 
 // Mean width of the slices below which they count as narrow: program graphs have
-// 3.2, chains with rows of 1 to 8 entries 4.7 (both measured at SliceShape).
+// 3.2, chains with rows of 1 to 8 entries 4.7 (both measured at SliceShape).  In
+// FP64 only sets with band tiles do: with whole windows or none the wide shape is
+// faster on narrow slices too (92 chains of 17,557 states, 2.5 entries per row, us
+// per product: 24.4 and 23.0 narrow, 19.8 and 19.3 wide; one chain of 1.76 M states
+// 79 and 77 per sweep; the band of a 2 M-state program graph 22.4 and 26.3).
 constexpr int kNarrowSlots = 4;
+// Slices per tile up to which a wavefront has few (two on average).  Program graphs,
+// us per FP64 sweep, few / narrow shape: 60,000 states 6.8 / 7.3, 276,253 (17 slices
+// per tile) 8.0 / 10.1, 500,000 (31) 9.7 / 11.1, 1 M (61) 16.2 / 14.6; FP32 232,672
+// states (7) 9.0 / 9.2, 404,694 9.6 / 9.9, 800,000 (25) 11.3 / 11.3.
+constexpr int kFewSlices = 2 * TNT / 64;
 
 // Sliced rows of the tile set for T and the forward or transposed matrix,
 // built once: a block per tile orders its rows and measures its slices, the
@@ -1480,7 +1489,6 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   ss.v.wide = ss.wide.p;
   ss.v.nslice = nslice;
   ss.v.nslot = (int32_t)(total + pent);
-  ss.v.narrow = total < (int64_t)kNarrowSlots * SLICE * nslice ? 1 : 0;
   HIPCHK(ctx, launch_set_i32(st, ss.far.p, 0));  // read where a slice has none
   up.run();
   HIPCHK(ctx, launch_slice_fill<T>(st, m, tl, stile_d.p, ss.v, far0_d.p, nfar_d.p));
@@ -1490,6 +1498,10 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   const double slice_bytes = (double)total * (double)((exact ? sizeof(float) : sizeof(T)) + (any32 ? 4 : 2)) +
                              (double)pent * (double)(sizeof(T) + 2) + (double)ncnt;
   ss.v.stream = slice_bytes > kStreamBytes ? 1 : 0;
+  const bool narrow = total < (int64_t)kNarrowSlots * SLICE * nslice;
+  if (npaneled > 0) ss.v.shape = SLICES_WIDE;
+  else if (!ss.v.stream && nslice <= kFewSlices * nt && (sizeof(T) == 8 || narrow)) ss.v.shape = SLICES_FEW;
+  else ss.v.shape = narrow && (sizeof(T) == 4 || any_band) ? SLICES_NARROW : SLICES_WIDE;
   if (npaneled > 0) {
     HIPCHK(ctx, hipMemsetAsync(ss.val.p + (total + pent), 0, sizeof(T) * PANEL_SLACK, st));
     HIPCHK(ctx, hipMemsetAsync(ss.c16.p + (total + pent), 0, sizeof(uint16_t) * PANEL_SLACK, st));

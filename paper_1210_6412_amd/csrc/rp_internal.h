@@ -133,8 +133,11 @@ struct Sliced {
   const int32_t* wide;   // [ntile] 1: 32-bit columns
   int32_t nslice;
   int32_t nslot;
-  int32_t narrow;        // 1: slices of up to about four entries
+  int32_t shape;         // SLICES_*
 };
+// How a wavefront takes its slices: wide or narrow ones, or few of them (see
+// SliceShape).
+enum : int { SLICES_WIDE = 0, SLICES_NARROW = 1, SLICES_FEW = 2 };
 // Most slices a wavefront of a paneled tile keeps sums for (rows of a paneled
 // tile <= PanelShape<T>::MAXS * 1024): a quarter of the 128 registers a lane
 // has at 16 wavefronts per CU for FP64 sums, and as many slices in FP32,

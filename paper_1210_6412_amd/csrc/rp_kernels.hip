@@ -1356,12 +1356,12 @@ __device__ __forceinline__ bool jacobi_rows(const MatView<T>& m, const T* __rest
 // threshold are loaded before the window copy so that their latency overlaps
 // it (the copy is wasted only on the sweep that stops).  Returns false when
 // the instance stops (uniform over the block).
-template <typename T>
+template <typename T, typename Mid>
 __device__ __forceinline__ bool jacobi_begin(T* xs, const T* __restrict__ x, const Tiles& tl, int c, int inst, int kind,
                                              int w0, int nw, int64_t s, const double* __restrict__ pprev,
                                              int32_t* status, int64_t* iters, double* meas,
                                              const double* __restrict__ thr, int strict, int64_t max_iter,
-                                             int32_t* ndone) {
+                                             int32_t* ndone, Mid mid) {
   double pv = 0.0, th = 0.0;
   if (s > 0) {
     const int t = tl.inst_t0[inst] + (threadIdx.x & 63);
@@ -1369,6 +1369,7 @@ __device__ __forceinline__ bool jacobi_begin(T* xs, const T* __restrict__ x, con
     th = thr[inst];
   }
   if (kind != WIN_NONE) stage_window<T, TNT>(xs, x, w0, nw);
+  mid();
   if (s > 0 && jacobi_decide(tl, c, inst, s, pprev, pv, th, status, iters, meas, strict, max_iter, ndone) != ST_RUN)
     return false;
   if (kind != WIN_NONE) __syncthreads();
@@ -1392,7 +1393,7 @@ __global__ __launch_bounds__(TNT) void k_jacobi_tile(MatView<T> m, const T* __re
   const int64_t s = s_rel + (tl.sbase ? *tl.sbase : 0);
   auto begin = [&]() {
     return jacobi_begin<T>(xs, x, tl, c, inst, kind, w0, nw, s, pprev, status, iters, meas, thr, strict, max_iter,
-                           ndone);
+                           ndone, [] {});
   };
   if (!TileShape<T, L>::EARLY && !begin()) return;
   double mloc;
@@ -2878,32 +2879,46 @@ __device__ __forceinline__ void spmv_panel_rows(const Sliced<T>& sl, T* __restri
 
 // Slices and entries of each under way at a time.  SKIP: no load past a slice's
 // width or a wavefront's last slice (a branch each); else those loads read zeros.
-// NARROW sets have slices of up to about four entries, so that one chunk holds a
+// SLICES_NARROW: slices of up to about four entries, so that one chunk holds a
 // slice.  us per sweep, narrow / wide shape: 33.5 M-state program graph (3
 // entries per row) FP64 451 / 580, FP32 350 / 406; 64 chains of 20,000 (7.3 per
 // row) FP64 34.1 / 28.0, FP32 19.8 / 18.3; 500 chains of 16,000 (4.5 per row; wide)
 // FP64 137 / 127, FP32 75.7 / 72.6.  Reading zeros is slower in FP32 also on narrow
 // slices (357).  In FP64 8 x 2 sweeps the last at 120, but the 64 chains at 29.6.
-template <typename T, bool NARROW>
+// SLICES_FEW: about two slices per wavefront.  A wide group is then mostly empty, and
+// the sweep is a chain of latencies, fetching its instructions among them: the code
+// is kept short and a wavefront's last group reads nothing ahead (a branch that the
+// other shapes do better without: 64 chains FP64 27.4 without, 28.9 with it).
+template <typename T, int SHAPE>
 struct SliceShape;
 template <>
-struct SliceShape<double, false> {  // one 1024-thread block per CU: registers to spare
+struct SliceShape<double, SLICES_WIDE> {  // one 1024-thread block per CU: registers to spare
   static constexpr int U = 4, NS = 4;
   static constexpr bool SKIP = true;
 };
 template <>
-struct SliceShape<double, true> {
+struct SliceShape<double, SLICES_NARROW> {
   static constexpr int U = 4, NS = 4;
   static constexpr bool SKIP = false;
 };
 template <>
-struct SliceShape<float, false> {  // two blocks per CU: at most 64 VGPRs
+struct SliceShape<float, SLICES_WIDE> {  // two blocks per CU: at most 64 VGPRs
   static constexpr int U = 8, NS = 1;
   static constexpr bool SKIP = true;
 };
 template <>
-struct SliceShape<float, true> {
+struct SliceShape<float, SLICES_NARROW> {
   static constexpr int U = 4, NS = 2;
+  static constexpr bool SKIP = true;
+};
+template <>
+struct SliceShape<double, SLICES_FEW> {
+  static constexpr int U = 4, NS = 2;
+  static constexpr bool SKIP = true;
+};
+template <>
+struct SliceShape<float, SLICES_FEW> {
+  static constexpr int U = 4, NS = 1;
   static constexpr bool SKIP = true;
 };
 
@@ -2921,7 +2936,8 @@ __device__ __forceinline__ const VT* slice_values(const Sliced<T>& sl) {
 // records.  The sweep is bound by the memory rate as long as enough loads are
 // under way, and with one block per compute unit (an FP64 window fills its LDS)
 // that is a question of how many loads wait for others: the records are read
-// once, a lane each, before the window is staged, the row numbers (and the
+// once, a lane each, before the window is staged (the first columns of far
+// entries, which wait for them, behind its loads), the row numbers (and the
 // columns of far entries) of the next slices while the current ones' entries
 // are under way, so that a group of NS slices costs one memory latency instead
 // of three, and no load is conditional (a compiler's wait after a branch is a
@@ -2937,16 +2953,15 @@ __device__ __forceinline__ const VT* slice_values(const Sliced<T>& sl) {
 // without the order of the loads made the first one slower (706).  The path by
 // column form is chosen after the window is staged: chosen before, its threefold
 // code took 5 us more per FP32 launch.
-template <typename T, bool NARROW>
+template <typename T, int SHAPE>
 struct SliceRows {
-  static constexpr int U = SliceShape<T, NARROW>::U, NS = SliceShape<T, NARROW>::NS, NW = TNT / 64;
-  static constexpr bool SKIP = SliceShape<T, NARROW>::SKIP;
+  static constexpr int U = SliceShape<T, SHAPE>::U, NS = SliceShape<T, SHAPE>::NS, NW = TNT / 64;
+  static constexpr bool SKIP = SliceShape<T, SHAPE>::SKIP;
   SliceRec m;  // of the wavefront's slice `lane`
   int wave, lane, sb, n;
   int next_row[NS], next_far[NS];  // of the next group
 
-  // band: the slices may have far entries
-  __device__ __forceinline__ SliceRows(const Sliced<T>& sl, int sb_, int se, bool band) {
+  __device__ __forceinline__ SliceRows(const Sliced<T>& sl, int sb_, int se) {
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     lane = threadIdx.x & 63;
     sb = sb_;
@@ -2955,7 +2970,6 @@ struct SliceRows {
     m = SliceRec{0, SLICE_UNIT, 0, 0};
     if (lane < n) m = sl.rec[sb + wave * per + min(wave, rem) + lane];
     rows(sl, 0);
-    if (band) far(sl, 0);
   }
   // row numbers (0xFFFF: none) and columns of far entries of group i
   __device__ __forceinline__ void rows(const Sliced<T>& sl, int i) {
@@ -2974,9 +2988,9 @@ struct SliceRows {
     }
   }
 };
-template <typename T, typename VT, int COL, bool NT, bool NARROW>
-struct SlicePipe : SliceRows<T, NARROW> {
-  using R = SliceRows<T, NARROW>;
+template <typename T, typename VT, int COL, bool NT, int SHAPE>
+struct SlicePipe : SliceRows<T, SHAPE> {
+  using R = SliceRows<T, SHAPE>;
   using R::U, R::NS, R::NW, R::SKIP, R::m, R::wave, R::lane, R::sb, R::n, R::next_row, R::next_far;
   int row[NS];  // of the group being swept
   int off[NS], W[NS], Wm, nfar[NS];
@@ -3005,7 +3019,7 @@ struct SlicePipe : SliceRows<T, NARROW> {
       nfar[q] = COL == COL_FAR && ok ? __builtin_amdgcn_readlane(m.nfar, e) : 0;
       Wm = max(Wm, W[q]);
       row[q] = next_row[q];
-      if (COL == COL_FAR) xf[q] = x[next_far[q]];
+      if (COL == COL_FAR && (SHAPE != SLICES_FEW || nfar[q] > 0)) xf[q] = x[next_far[q]];
       d[q] = (T)1;
       if (!SKIP || !unit[q]) d[q] = sl.d[(size_t)(unit[q] ? sl.nslice : sb + wave + (i + q) * NW) * SLICE + lane];
     }
@@ -3053,14 +3067,14 @@ struct SlicePipe : SliceRows<T, NARROW> {
 };
 
 // Jacobi rows of a tile's slices.
-template <typename T, typename VT, int COL, bool NT, bool NARROW>
-__device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const SliceRows<T, NARROW>& rows,
+template <typename T, typename VT, int COL, bool NT, int SHAPE>
+__device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const SliceRows<T, SHAPE>& rows,
                                                      const T* __restrict__ rhs, const T* __restrict__ xs,
                                                      const T* __restrict__ x, T* __restrict__ xn, int row0, int w0,
                                                      int nw, int weighted) {
-  constexpr int U = SliceRows<T, NARROW>::U, NS = SliceRows<T, NARROW>::NS;
+  constexpr int U = SliceRows<T, SHAPE>::U, NS = SliceRows<T, SHAPE>::NS;
   double mloc = 0.0;
-  SlicePipe<T, VT, COL, NT, NARROW> g(rows);
+  SlicePipe<T, VT, COL, NT, SHAPE> g(rows);
   for (int i = 0; i < g.n; i += NS) {
     T b[NS], acc[NS];
 #pragma unroll
@@ -3069,7 +3083,7 @@ __device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const 
       acc[q] = 0;
     }
     g.begin(sl, x, i);
-    g.next(sl, i + NS);
+    if (SHAPE != SLICES_FEW || i + NS < g.n) g.next(sl, i + NS);
     g.add(acc, xs, x, nw, w0);
     for (int j = U; j < g.Wm; j += U) {
       g.load(sl, j);
@@ -3089,7 +3103,7 @@ __device__ __forceinline__ double jacobi_sliced_rows(const Sliced<T>& sl, const 
   return mloc;
 }
 
-template <typename T, bool NT, bool PANEL, bool NARROW, typename VT>
+template <typename T, bool NT, bool PANEL, int SHAPE, typename VT>
 __global__ __launch_bounds__(TNT) void k_jacobi_sliced(Sliced<T> sl, const T* __restrict__ rhs,
                                                        const T* __restrict__ x, T* __restrict__ xn, Tiles tl, int64_t s_rel,
                                                        const double* __restrict__ pprev, double* __restrict__ pcur,
@@ -3105,43 +3119,55 @@ __global__ __launch_bounds__(TNT) void k_jacobi_sliced(Sliced<T> sl, const T* __
   if (status[inst] != ST_RUN) return;
   const int64_t s = s_rel + (tl.sbase ? *tl.sbase : 0);
   const int r0 = tl.row0[c], wide = sl.wide[c];
-  const SliceRows<T, NARROW> rows(sl, sb, se, kind == WIN_BAND);
-  if (!jacobi_begin<T>(xs, x, tl, c, inst, kind, w0, nw, s, pprev, status, iters, meas, thr, strict, max_iter, ndone))
+  SliceRows<T, SHAPE> rows(sl, sb, se);
+  if (!jacobi_begin<T>(xs, x, tl, c, inst, kind, w0, nw, s, pprev, status, iters, meas, thr, strict, max_iter, ndone,
+                       [&] { if (kind == WIN_BAND) rows.far(sl, 0); }))
     return;
   double mloc;
   if (PANEL && sl.npan[c] > 0) mloc = jacobi_panel_rows<T>(sl, rhs, xs, x, xn, c, sb, se, w0, weighted);
-  else if (wide) mloc = jacobi_sliced_rows<T, VT, COL_WIDE, NT, NARROW>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
-  else if (kind == WIN_WHOLE) mloc = jacobi_sliced_rows<T, VT, COL_IN, NT, NARROW>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
-  else mloc = jacobi_sliced_rows<T, VT, COL_FAR, NT, NARROW>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
+  else if (wide) mloc = jacobi_sliced_rows<T, VT, COL_WIDE, NT, SHAPE>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
+  else if (kind == WIN_WHOLE) mloc = jacobi_sliced_rows<T, VT, COL_IN, NT, SHAPE>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
+  else mloc = jacobi_sliced_rows<T, VT, COL_FAR, NT, SHAPE>(sl, rows, rhs, xs, x, xn, r0, w0, nw, weighted);
   double v[1] = {mloc};
   block_reduce<1, TNT>(v, 1u);
   if (threadIdx.x == 0) pcur[c] = v[0];
 }
 
-// Which instance of the sliced kernels: streamed or not, and paneled (never
-// narrow), or narrow and with FP32 values or not.
-template <typename T>
-static int slice_variant(const Sliced<T>& sl) {
-  return (sl.stream ? 1 : 0) + (sl.paneled ? 2 : (sl.val32 ? (sl.narrow ? 8 : 4) : (sl.narrow ? 6 : 0)));
+// The kernel of a set, called as run(number, streamed, paneled, shape, value type):
+// paneled sets are of the wide shape and hold values of T, streamed ones never few.
+template <typename T, typename Run>
+static hipError_t slice_variant(const Sliced<T>& sl, Run run) {
+  using std::false_type;
+  using std::true_type;
+  using Wide = std::integral_constant<int, SLICES_WIDE>;
+  using Narrow = std::integral_constant<int, SLICES_NARROW>;
+  using Few = std::integral_constant<int, SLICES_FEW>;
+  auto by_value = [&](int v, auto nt, auto shape) {
+    return sl.val32 ? run(v, nt, false_type{}, shape, float{}) : run(v + 1, nt, false_type{}, shape, T{});
+  };
+  if (sl.paneled)
+    return sl.stream ? run(0, true_type{}, true_type{}, Wide{}, T{}) : run(1, false_type{}, true_type{}, Wide{}, T{});
+  if (sl.shape == SLICES_FEW) return by_value(2, false_type{}, Few{});
+  if (sl.shape == SLICES_NARROW)
+    return sl.stream ? by_value(4, true_type{}, Narrow{}) : by_value(6, false_type{}, Narrow{});
+  return sl.stream ? by_value(8, true_type{}, Wide{}) : by_value(10, false_type{}, Wide{});
 }
+constexpr int SLICE_VARIANTS = 12;
 
 template <typename T>
 hipError_t launch_jacobi_sliced(hipStream_t st, Sliced<T> sl, const T* rhs, const T* x, T* xn, Tiles tl, int64_t s,
                                 const double* pprev, double* pcur, int32_t* status, int64_t* iters, double* meas,
                                 const double* thr, int strict, int64_t max_iter, int32_t* ndone, int weighted) {
   const size_t lds = (size_t)max(tl.maxw, sl.paneled ? sl.pw : 0) * sizeof(T);
-  static size_t conf[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const int v = slice_variant(sl);
-  const auto kern = v == 0 ? k_jacobi_sliced<T, false, false, false, T> : v == 1 ? k_jacobi_sliced<T, true, false, false, T>
-                  : v == 2 ? k_jacobi_sliced<T, false, true, false, T> : v == 3 ? k_jacobi_sliced<T, true, true, false, T>
-                  : v == 4 ? k_jacobi_sliced<T, false, false, false, float> : v == 5 ? k_jacobi_sliced<T, true, false, false, float>
-                  : v == 6 ? k_jacobi_sliced<T, false, false, true, T> : v == 7 ? k_jacobi_sliced<T, true, false, true, T>
-                  : v == 8 ? k_jacobi_sliced<T, false, false, true, float> : k_jacobi_sliced<T, true, false, true, float>;
-  hipError_t e = set_lds(kern, lds, conf[v]);
-  if (e != hipSuccess) return e;
-  kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, rhs, x, xn, tl, s, pprev, pcur, status, iters, meas, thr, strict,
-                                             max_iter, ndone, weighted);
-  return hipGetLastError();
+  static size_t conf[SLICE_VARIANTS] = {};
+  return slice_variant(sl, [&](int v, auto nt, auto panel, auto shape, auto value) {
+    const auto kern = k_jacobi_sliced<T, nt.value, panel.value, shape.value, decltype(value)>;
+    hipError_t e = set_lds(kern, lds, conf[v]);
+    if (e != hipSuccess) return e;
+    kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, rhs, x, xn, tl, s, pprev, pcur, status, iters, meas, thr, strict,
+                                               max_iter, ndone, weighted);
+    return hipGetLastError();
+  });
 }
 template hipError_t launch_jacobi_sliced<double>(hipStream_t, Sliced<double>, const double*, const double*, double*,
                                                  Tiles, int64_t, const double*, double*, int32_t*, int64_t*, double*,
@@ -3162,7 +3188,7 @@ template <typename T, typename VT>
 __device__ __forceinline__ double resident_sliced_rows(const Sliced<T>& sl, const T* __restrict__ rhs,
                                                        const T* cur, T* nxt, int sb, int se, int r0,
                                                        int weighted) {
-  constexpr int U = SliceShape<T, false>::U, NS = SliceShape<T, false>::NS, NW = TNT / 64;
+  constexpr int U = SliceShape<T, SLICES_WIDE>::U, NS = SliceShape<T, SLICES_WIDE>::NS, NW = TNT / 64;
   const VT* __restrict__ val = slice_values<T, VT>(sl);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   double mloc = 0.0;
@@ -3281,12 +3307,12 @@ template hipError_t launch_jacobi_resident_sliced<float>(hipStream_t, Sliced<flo
 // y = d u - A_off u on sliced rows, with the dot products of the lane-group
 // kernel (MODE 0: q.y; MODE 1: y.u and y.y), or (MODE 2) the FP64 residual
 // y <- qv - y of the refinement with its max |.| (qv is then b).
-template <typename T, typename VT, int MODE, int COL, bool NT, bool NARROW>
-__device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const SliceRows<T, NARROW>& rows,
+template <typename T, typename VT, int MODE, int COL, bool NT, int SHAPE>
+__device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const SliceRows<T, SHAPE>& rows,
                                                  const T* __restrict__ us, const T* __restrict__ u, T* __restrict__ y,
                                                  const T* __restrict__ qv, int row0, int w0, int nw, double* a) {
-  constexpr int U = SliceRows<T, NARROW>::U, NS = SliceRows<T, NARROW>::NS;
-  SlicePipe<T, VT, COL, NT, NARROW> g(rows);
+  constexpr int U = SliceRows<T, SHAPE>::U, NS = SliceRows<T, SHAPE>::NS;
+  SlicePipe<T, VT, COL, NT, SHAPE> g(rows);
   for (int i = 0; i < g.n; i += NS) {
     T b[NS], acc[NS];
 #pragma unroll
@@ -3295,7 +3321,7 @@ __device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const Slic
       acc[q] = 0;
     }
     g.begin(sl, u, i);
-    g.next(sl, i + NS);
+    if (SHAPE != SLICES_FEW || i + NS < g.n) g.next(sl, i + NS);
     g.add(acc, us, u, nw, w0);
     for (int j = U; j < g.Wm; j += U) {
       g.load(sl, j);
@@ -3324,7 +3350,7 @@ __device__ __forceinline__ void spmv_sliced_rows(const Sliced<T>& sl, const Slic
   }
 }
 
-template <typename T, int MODE, bool NT, bool PANEL, bool NARROW, typename VT>
+template <typename T, int MODE, bool NT, bool PANEL, int SHAPE, typename VT>
 __global__ __launch_bounds__(TNT) void k_spmv_sliced(Sliced<T> sl, const T* __restrict__ u, T* __restrict__ y,
                                                      const T* __restrict__ qv, Tiles tl,
                                                      const int32_t* __restrict__ status, double* __restrict__ part) {
@@ -3335,16 +3361,17 @@ __global__ __launch_bounds__(TNT) void k_spmv_sliced(Sliced<T> sl, const T* __re
   const int w0 = tl.w0[c], nw = tl.nw[c], kind = tl.kind[c];
   const int sb = sl.t_s0[c], se = sl.t_s0[c + 1];
   const int r0 = tl.row0[c], wide = sl.wide[c];
-  const SliceRows<T, NARROW> rows(sl, sb, se, kind == WIN_BAND);
+  SliceRows<T, SHAPE> rows(sl, sb, se);
   if (kind != WIN_NONE) {
     stage_window<T, TNT>(us, u, w0, nw);
+    if (kind == WIN_BAND) rows.far(sl, 0);
     __syncthreads();
   }
   double a[2] = {0.0, 0.0};
   if (PANEL && sl.npan[c] > 0) spmv_panel_rows<T, MODE>(sl, us, u, y, qv, c, sb, se, w0, a);
-  else if (wide) spmv_sliced_rows<T, VT, MODE, COL_WIDE, NT, NARROW>(sl, rows, us, u, y, qv, r0, w0, nw, a);
-  else if (kind == WIN_WHOLE) spmv_sliced_rows<T, VT, MODE, COL_IN, NT, NARROW>(sl, rows, us, u, y, qv, r0, w0, nw, a);
-  else spmv_sliced_rows<T, VT, MODE, COL_FAR, NT, NARROW>(sl, rows, us, u, y, qv, r0, w0, nw, a);
+  else if (wide) spmv_sliced_rows<T, VT, MODE, COL_WIDE, NT, SHAPE>(sl, rows, us, u, y, qv, r0, w0, nw, a);
+  else if (kind == WIN_WHOLE) spmv_sliced_rows<T, VT, MODE, COL_IN, NT, SHAPE>(sl, rows, us, u, y, qv, r0, w0, nw, a);
+  else spmv_sliced_rows<T, VT, MODE, COL_FAR, NT, SHAPE>(sl, rows, us, u, y, qv, r0, w0, nw, a);
   if (MODE != 1) {
     double b1[1] = {a[0]};
     block_reduce<1, TNT>(b1, MODE == 2 ? 1u : 0u);
@@ -3362,17 +3389,14 @@ template <typename T, int MODE>
 static hipError_t spmv_sliced_M(hipStream_t st, Sliced<T> sl, const T* u, T* y, const T* qv, Tiles tl,
                                 const int32_t* status, double* part) {
   const size_t lds = (size_t)max(tl.maxw, sl.paneled ? sl.pw : 0) * sizeof(T);
-  static size_t conf[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const int v = slice_variant(sl);
-  const auto kern = v == 0 ? k_spmv_sliced<T, MODE, false, false, false, T> : v == 1 ? k_spmv_sliced<T, MODE, true, false, false, T>
-                  : v == 2 ? k_spmv_sliced<T, MODE, false, true, false, T> : v == 3 ? k_spmv_sliced<T, MODE, true, true, false, T>
-                  : v == 4 ? k_spmv_sliced<T, MODE, false, false, false, float> : v == 5 ? k_spmv_sliced<T, MODE, true, false, false, float>
-                  : v == 6 ? k_spmv_sliced<T, MODE, false, false, true, T> : v == 7 ? k_spmv_sliced<T, MODE, true, false, true, T>
-                  : v == 8 ? k_spmv_sliced<T, MODE, false, false, true, float> : k_spmv_sliced<T, MODE, true, false, true, float>;
-  hipError_t e = set_lds(kern, lds, conf[v]);
-  if (e != hipSuccess) return e;
-  kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, u, y, qv, tl, status, part);
-  return hipGetLastError();
+  static size_t conf[SLICE_VARIANTS] = {};
+  return slice_variant(sl, [&](int v, auto nt, auto panel, auto shape, auto value) {
+    const auto kern = k_spmv_sliced<T, MODE, nt.value, panel.value, shape.value, decltype(value)>;
+    hipError_t e = set_lds(kern, lds, conf[v]);
+    if (e != hipSuccess) return e;
+    kern<<<(unsigned)tl.ntile, TNT, lds, st>>>(sl, u, y, qv, tl, status, part);
+    return hipGetLastError();
+  });
 }
 template <typename T>
 hipError_t launch_spmv_sliced(hipStream_t st, int mode, Sliced<T> sl, const T* u, T* y, const T* qv, Tiles tl,
