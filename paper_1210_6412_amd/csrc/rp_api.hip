@@ -2580,6 +2580,12 @@ void partition_searches(rp_context* ctx, const rp_chain* chain, const uint8_t* g
   }
 }
 
+// Mean row length from which the kernels that lay the rows out read several runs of
+// a row at once.  us for row counts / rows, one run at a time and four: 9.6 M states
+// of 4.5 entries 460 / 712 and 528 / 834; 1.28 M of 8.5 106 / 120 and 107 / 131;
+// 640,000 of 16 105 / 113 and 105 / 94; 4,000 of 400 41 / 38 and 31 / 21.
+constexpr int64_t kReadAheadRow = 12;
+
 // Reduced system of a classified chain (s->cls set, flags_sq[i] = 1 for the
 // states of S_?): numbering with instance blocks padded to PAD rows, the
 // off-diagonal CSR with d = 1 - P(s,s) and b = P(s, S_{=1}) (Section 2.3),
@@ -2625,8 +2631,9 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   dalloc(ctx, s->d64, (size_t)np);
   dalloc(ctx, s->d32, (size_t)np);
   dalloc(ctx, s->b64, (size_t)np);
+  const int ahead = nnz >= kReadAheadRow * n ? 1 : 0;
   HIPCHK(ctx, launch_row_count(st, np, s->row_state.p, chain->row_ptr, chain->col, chain->val, s->cls.p, rcnt.p,
-                               s->d64.p, s->d32.p, s->b64.p, s->general ? 1 : 0));
+                               s->d64.p, s->d32.p, s->b64.p, s->general ? 1 : 0, ahead));
   dalloc(ctx, s->fwd.rp, (size_t)np + 1);
   DBuf<int32_t> scratch2;
   dalloc(ctx, scratch2, scan_scratch_elems(np));
@@ -2648,7 +2655,7 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   dalloc(ctx, s->fwd.v64, (size_t)z + 1);
   dalloc(ctx, s->fwd.v32, (size_t)z + 1);
   HIPCHK(ctx, launch_fill_rows(st, np, s->row_state.p, chain->row_ptr, chain->col, chain->val, s->cls.p, s->map.p,
-                               s->fwd.rp.p, s->fwd.col.p, s->fwd.v64.p, s->fwd.v32.p, s->general ? 1 : 0));
+                               s->fwd.rp.p, s->fwd.col.p, s->fwd.v64.p, s->fwd.v32.p, s->general ? 1 : 0, ahead));
 
   // keep P's structure for the gradient
   dalloc(ctx, s->prp, (size_t)n + 1);

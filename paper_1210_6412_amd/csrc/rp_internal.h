@@ -267,13 +267,14 @@ hipError_t launch_map(hipStream_t st, int64_t n, const uint8_t* cls, const int32
 hipError_t launch_row_count(hipStream_t st, int64_t npad, const int32_t* row_state,
                             const int32_t* rp, const int32_t* col, const double* val,
                             const uint8_t* cls, int32_t* cnt, double* d64, float* d32,
-                            double* b64, int any_sign);
+                            double* b64, int any_sign, int ahead);
 hipError_t launch_fill_rows(hipStream_t st, int64_t npad, const int32_t* row_state,
                             const int32_t* rp, const int32_t* col, const double* val,
                             const uint8_t* cls, const int32_t* map, const int32_t* arp,
-                            int32_t* acol, double* av64, float* av32, int any_sign);
+                            int32_t* acol, double* av64, float* av32, int any_sign, int ahead);
 // (any_sign: keep every nonzero off-diagonal entry, not only P > 0: the
-// general systems of rp_matrix_system)
+// general systems of rp_matrix_system; ahead: several runs of a row's entries
+// are read at once, for long rows)
 // Transpose of the reduced matrix (npad rows, z entries): trp (npad + 1),
 // tcol / tv64 / tv32 (z).  Work arrays erow, idx, key_out, perm (z each) and
 // temp (transpose_temp_bytes) belong to the caller.

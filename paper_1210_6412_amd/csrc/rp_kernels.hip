@@ -117,11 +117,10 @@ __device__ __forceinline__ T row_sum(const MatView<T>& m, const T* __restrict__ 
 // in-group shuffles wherever a sum must follow the entry order exactly.
 constexpr int PG = 8;
 
-// Runs of PG entries of a row read ahead by the kernels that lay a system out
-// (row counts, rows): a run at a time waits for memory once or twice per PG
-// entries.  4,096 rows of 400 entries, us: row counts 46.9 -> 31.2, rows 51.9 ->
-// 21.2.  (Validation, whose checks take as long as its loads, was slower so: 45.7
-// -> 60.)
+// Runs of PG entries of a row read at once by the kernels that lay a system out (row
+// counts, rows) where rows are long: a run at a time waits for memory once or twice
+// per PG entries.  (Validation, whose checks take as long as its loads, was slower so:
+// 45.7 us -> 60 on 4,096 rows of 400 entries.)
 constexpr int PGA = 4;
 
 // Ordered sum over the group's PG lanes of q (lane 0's term first), added to acc.
@@ -613,6 +612,7 @@ hipError_t launch_map(hipStream_t st, int64_t n, const uint8_t* cls, const int32
 // Per reduced row: number of off-diagonal entries into S_?, d = 1 - P(s,s)
 // and b = P(s, S_{=1}) summed in storage order (Section 2.3).  Padding rows
 // get d = 1, b = 0 and no entries.
+template <int A>
 __global__ __launch_bounds__(BS) void k_row_count(int64_t npad, const int32_t* __restrict__ row_state,
                                                   const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                   const double* __restrict__ val, const uint8_t* __restrict__ cls,
@@ -629,20 +629,20 @@ __global__ __launch_bounds__(BS) void k_row_count(int64_t npad, const int32_t* _
   double pii = 0.0, bi = 0.0;
   int32_t c = 0;
   const int32_t k1 = rp[v + 1];
-  for (int32_t ka = rp[v]; ka < k1; ka += PG * PGA) {
-    int32_t t[PGA];
-    double p[PGA];
-    uint8_t ct[PGA];
+  for (int32_t ka = rp[v]; ka < k1; ka += PG * A) {
+    int32_t t[A];
+    double p[A];
+    uint8_t ct[A];
 #pragma unroll
-    for (int j = 0; j < PGA; j++) {
+    for (int j = 0; j < A; j++) {
       const int32_t k = min(ka + j * PG + l, k1 - 1);
       t[j] = col[k];
       p[j] = val[k];
     }
 #pragma unroll
-    for (int j = 0; j < PGA; j++) ct[j] = cls[t[j]];
+    for (int j = 0; j < A; j++) ct[j] = cls[t[j]];
 #pragma unroll
-    for (int j = 0; j < PGA; j++) {
+    for (int j = 0; j < A; j++) {
       if (ka + j * PG >= k1) break;
       const bool in = ka + j * PG + l < k1;
       const bool edge = in && t[j] != v && (any_sign ? p[j] != 0.0 : p[j] > 0.0);
@@ -658,12 +658,14 @@ __global__ __launch_bounds__(BS) void k_row_count(int64_t npad, const int32_t* _
 }
 hipError_t launch_row_count(hipStream_t st, int64_t npad, const int32_t* row_state, const int32_t* rp,
                             const int32_t* col, const double* val, const uint8_t* cls, int32_t* cnt,
-                            double* d64, float* d32, double* b64, int any_sign) {
+                            double* d64, float* d32, double* b64, int any_sign, int ahead) {
+  const auto kern = ahead ? k_row_count<PGA> : k_row_count<1>;
   if (npad > 0)
-    k_row_count<<<grid_for(npad * PG), BS, 0, st>>>(npad, row_state, rp, col, val, cls, cnt, d64, d32, b64, any_sign);
+    kern<<<grid_for(npad * PG), BS, 0, st>>>(npad, row_state, rp, col, val, cls, cnt, d64, d32, b64, any_sign);
   return hipGetLastError();
 }
 
+template <int A>
 __global__ __launch_bounds__(BS) void k_fill_rows(int64_t npad, const int32_t* __restrict__ row_state,
                                                   const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                   const double* __restrict__ val, const uint8_t* __restrict__ cls,
@@ -677,29 +679,29 @@ __global__ __launch_bounds__(BS) void k_fill_rows(int64_t npad, const int32_t* _
   if (v < 0) return;
   int32_t pos = arp[r];
   const int32_t k1 = rp[v + 1];
-  for (int32_t ka = rp[v]; ka < k1; ka += PG * PGA) {
-    int32_t t[PGA], mt[PGA];
-    double p[PGA];
-    uint8_t ct[PGA];
+  for (int32_t ka = rp[v]; ka < k1; ka += PG * A) {
+    int32_t t[A], mt[A];
+    double p[A];
+    uint8_t ct[A];
 #pragma unroll
-    for (int j = 0; j < PGA; j++) {
+    for (int j = 0; j < A; j++) {
       const int32_t k = min(ka + j * PG + l, k1 - 1);
       t[j] = col[k];
       p[j] = val[k];
     }
 #pragma unroll
-    for (int j = 0; j < PGA; j++) {
+    for (int j = 0; j < A; j++) {
       ct[j] = cls[t[j]];
-      mt[j] = map[t[j]];
+      if (A > 1) mt[j] = map[t[j]];
     }
 #pragma unroll
-    for (int j = 0; j < PGA; j++) {
+    for (int j = 0; j < A; j++) {
       if (ka + j * PG >= k1) break;
       const bool inc = ka + j * PG + l < k1 && t[j] != v && (any_sign ? p[j] != 0.0 : p[j] > 0.0) && ct[j] == 2;
       const unsigned gm = group_bits(inc);
       if (inc) {
         const int32_t q = pos + __popc(gm & ((1u << l) - 1u));
-        acol[q] = mt[j];
+        acol[q] = A > 1 ? mt[j] : map[t[j]];
         av64[q] = p[j];
         av32[q] = (float)p[j];
       }
@@ -709,10 +711,10 @@ __global__ __launch_bounds__(BS) void k_fill_rows(int64_t npad, const int32_t* _
 }
 hipError_t launch_fill_rows(hipStream_t st, int64_t npad, const int32_t* row_state, const int32_t* rp,
                             const int32_t* col, const double* val, const uint8_t* cls, const int32_t* map,
-                            const int32_t* arp, int32_t* acol, double* av64, float* av32, int any_sign) {
+                            const int32_t* arp, int32_t* acol, double* av64, float* av32, int any_sign, int ahead) {
+  const auto kern = ahead ? k_fill_rows<PGA> : k_fill_rows<1>;
   if (npad > 0)
-    k_fill_rows<<<grid_for(npad * PG), BS, 0, st>>>(npad, row_state, rp, col, val, cls, map, arp, acol, av64, av32,
-                                                    any_sign);
+    kern<<<grid_for(npad * PG), BS, 0, st>>>(npad, row_state, rp, col, val, cls, map, arp, acol, av64, av32, any_sign);
   return hipGetLastError();
 }
 
