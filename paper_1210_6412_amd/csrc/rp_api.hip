@@ -305,7 +305,17 @@ struct rp_system {
   // only: both iterates fit the LDS and a sweep moves little data)
   TileSet res64, res32;
   // the last running instances of a tiled Jacobi solve, resident (build_tail);
-  // on sliced rows with the slices of each: [tail_slo[c], tail_shi[c])
+  // on sliced rows with the slices of each: [tail_slo[c], tail_shi[c]) of the
+  // tiled sweeps' sliced rows or, where those run on cells, of tail64 / tail32
+  // (tail_slices; forward [0] and transposed [1] matrix)
+  template <typename T>
+  struct TailSlices {
+    TileSet ts;
+    SlicedSet<T> ss;
+    std::vector<int32_t> lo, hi;  // slices of instance k: [lo[k], hi[k]), empty where it has none
+  };
+  TailSlices<double> tail64[2];
+  TailSlices<float> tail32[2];
   TileSet tail;
   DBuf<int32_t> tail_slo, tail_shi;
   bool tail_sliced = false;
@@ -1129,44 +1139,47 @@ void build_resident(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, size_
 // counts, and the last few of a batch (often small chains that mix slowly)
 // can need as many sweeps again as the rest, each a launch over every tile
 // for one or two instances' rows.  Once at most kTailInstances still run and
-// each fits the resident kernel (the limits of build_resident), s->tail gets
-// one tile per running instance and the remaining sweeps run resident, many
-// per launch.  False (s->tail untouched) when none runs or one does not fit.
-// With the slice starts of the tiled sweeps' sliced rows (t_s0_h, per tile of
-// `main`), and every tile of the running instances a whole-block window, the
-// tail keeps the sliced rows (s->tail_sliced, slices in s->tail_slo/shi).
+// each fits the resident kernel (the limits of build_resident), the remaining
+// sweeps run resident, many per launch.
 constexpr int kTailInstances = 16;
 
-bool build_tail(rp_context* ctx, rp_system* s, size_t width, const std::vector<int32_t>& status_h,
-                const rp_system::TileSet& main, const std::vector<int32_t>* t_s0_h) {
-  Uploads up(ctx);
-  const int K = s->K;
+// The running instances, or none when one of them does not fit.
+std::vector<int32_t> tail_instances(const rp_system* s, size_t width, const std::vector<int32_t>& status_h) {
   const double w = (double)width;
-  std::vector<int32_t> trow0, tnr, tinst, tkind, tc0(K + 1, 0);
-  int64_t maxw = 0;
-  for (int k = 0; k < K; k++) {
-    tc0[k] = (int32_t)trow0.size();
+  std::vector<int32_t> who;
+  for (int k = 0; k < s->K; k++) {
     const int64_t rows = s->roff_h[k + 1] - s->roff_h[k];
     if (status_h[k] != ST_RUN || rows == 0) continue;
     const double sweep_bytes = (2.0 + w) * (double)s->z_h[k] + (4.0 + 4.0 * w) * (double)s->nq_h[k];
-    if (rows > 65536 || 2.0 * w * (double)rows > (double)TILE_LDS_BYTES || sweep_bytes > kResidentBytes) return false;
+    if (rows > 65536 || 2.0 * w * (double)rows > (double)TILE_LDS_BYTES || sweep_bytes > kResidentBytes) return {};
+    who.push_back(k);
+  }
+  return who;
+}
+
+// s->tail: one tile per instance of `who`; on sliced rows where [lo[k], hi[k])
+// are the slices of each such instance k (one without any: none is).
+void build_tail(rp_context* ctx, rp_system* s, const std::vector<int32_t>& who, const std::vector<int32_t>& lo,
+                const std::vector<int32_t>& hi) {
+  Uploads up(ctx);
+  const int K = s->K;
+  std::vector<int32_t> trow0, tnr, tkind, tc0(K + 1, 0), slo, shi;
+  const std::vector<int32_t>& tinst = who;
+  int64_t maxw = 0;
+  bool sliced = !lo.empty();
+  for (int32_t k : who) {
+    const int64_t rows = s->roff_h[k + 1] - s->roff_h[k];
     maxw = std::max(maxw, rows);
     trow0.push_back((int32_t)s->roff_h[k]);
     tnr.push_back((int32_t)rows);
-    tinst.push_back(k);
     tkind.push_back(WIN_WHOLE);
+    for (int j = k + 1; j <= K; j++) tc0[j]++;
+    if (!sliced) continue;
+    slo.push_back(lo[k]);
+    shi.push_back(hi[k]);
+    sliced = lo[k] < hi[k];
   }
-  tc0[K] = (int32_t)trow0.size();
   const int32_t nt = tc0[K];
-  if (nt == 0) return false;
-  std::vector<int32_t> slo, shi;
-  bool sliced = t_s0_h != nullptr;
-  for (int32_t c = 0; c < nt && sliced; c++) {
-    const int k = tinst[c];
-    for (int32_t t = main.inst0_h[k]; t < main.inst0_h[k + 1]; t++) sliced = sliced && main.kind_h[t] == WIN_WHOLE;
-    slo.push_back((*t_s0_h)[main.inst0_h[k]]);
-    shi.push_back((*t_s0_h)[main.inst0_h[k + 1]]);
-  }
   if (sliced) {
     dalloc(ctx, s->tail_slo, (size_t)nt);
     dalloc(ctx, s->tail_shi, (size_t)nt);
@@ -1189,7 +1202,6 @@ bool build_tail(rp_context* ctx, rp_system* s, size_t width, const std::vector<i
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.row0.p, ts.nrows.p, ts.kind.p, nt, K, (int32_t)maxw};
   up.run();
   ts.ok = true;
-  return true;
 }
 
 // Chunk view of a tile set (same per-instance partial layout), for the
@@ -1300,27 +1312,21 @@ constexpr int kNarrowSlots = 4;
 // states (7) 9.0 / 9.2, 404,694 9.6 / 9.9, 800,000 (25) 11.3 / 11.3.
 constexpr int kFewSlices = 2 * TNT / 64;
 
-// Sliced rows of the tile set for T and the forward or transposed matrix,
-// built once: a block per tile orders its rows and measures its slices, the
-// host lays the slices out (64-bit offsets, checked against int32), and a
-// wavefront per slice copies the entries.  Returns false (the lane-group
-// tiles are used) when the tile set is absent or the slices would not fit
-// 32-bit offsets.
+// Sliced rows of a tile set and the forward or transposed matrix: a block per
+// tile orders its rows and measures its slices, the host lays the slices out
+// (64-bit offsets, checked against int32), and a wavefront per slice copies the
+// entries.  FP64 values are held in FP32 where that is exact for all of the
+// matrix, if `compact`.  Returns false when the slices would not fit 32-bit
+// offsets.
 template <typename T>
-bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
-  SlicedSet<T>& ss = sliced_for<T>(s, tr);
-  if (ss.built) return ss.ok;
-  rp_system::TileSet& ts = tiles_for<T>(s);
-  if (!ts.ok) {
-    ss.built = true;
-    return false;
-  }
-  if (tr) ensure_transpose(ctx, s);
+bool build_slices(rp_context* ctx, rp_system* s, bool tr, const rp_system::TileSet& ts, SlicedSet<T>& ss, bool compact,
+                  std::vector<int32_t>& t_s0) {
   hipStream_t st = ctx->stream;
   Uploads up(ctx);
   const Tiles& tl = ts.tl;
   const int32_t nt = tl.ntile;
-  std::vector<int32_t> t_s0(nt + 1, 0), stile;
+  std::vector<int32_t> stile;
+  t_s0.assign(nt + 1, 0);
   for (int32_t t = 0; t < nt; t++) {
     const int32_t ns = (ts.nrows_h[t] + SLICE - 1) / SLICE;
     t_s0[t + 1] = t_s0[t] + ns;
@@ -1452,7 +1458,7 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   const int64_t nent = total + pent + std::max(SLICE, PANEL_SLACK);
   bool exact = false;
   if constexpr (std::is_same<T, double>::value) {
-    if (npaneled == 0) {
+    if (compact && npaneled == 0) {
       dalloc(ctx, inexact, 1);
       HIPCHK(ctx, launch_set_i32(st, inexact.p, 0));
       HIPCHK(ctx, launch_inexact32(st, m.val, s->z, inexact.p));
@@ -1518,6 +1524,106 @@ bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
   ss.npaneled = npaneled;
   if (npaneled > 0) ss.npan_h = npan;
   ss.ok = true;
+  return true;
+}
+
+// Sliced rows of the tile set for T, built once.  Returns false (the lane-group
+// tiles are used) when the tile set is absent or the slices do not fit.
+template <typename T>
+bool ensure_sliced(rp_context* ctx, rp_system* s, bool tr) {
+  SlicedSet<T>& ss = sliced_for<T>(s, tr);
+  if (ss.built) return ss.ok;
+  const rp_system::TileSet& ts = tiles_for<T>(s);
+  if (!ts.ok) {
+    ss.built = true;
+    return false;
+  }
+  if (tr) ensure_transpose(ctx, s);
+  std::vector<int32_t> t_s0;
+  return build_slices<T>(ctx, s, tr, ts, ss, true, t_s0);
+}
+
+template <typename T>
+rp_system::TailSlices<T>& tail_slices_for(rp_system* s, bool tr);
+template <>
+rp_system::TailSlices<double>& tail_slices_for<double>(rp_system* s, bool tr) { return s->tail64[tr ? 1 : 0]; }
+template <>
+rp_system::TailSlices<float>& tail_slices_for<float>(rp_system* s, bool tr) { return s->tail32[tr ? 1 : 0]; }
+
+// build(), which returns whether it succeeded, or false where the memory for it
+// cannot be had: what it builds is then done without.
+template <typename Build>
+bool if_memory_allows(rp_context* ctx, Build build) {
+  const std::string err = ctx->err;
+  try {
+    return build();
+  } catch (const Fail& f) {
+    if (f.code != RP_ERR_OOM) throw;
+    ctx->err = err;
+    (void)hipGetLastError();  // not for the next launch to report
+    return false;
+  }
+}
+
+// Sliced rows of the tail's instances, for sweeps that ran on cells: resident
+// sweeps on one lane per row wait for a long row's entries one after another
+// (256 sweeps of the last chains of 256 with 1,000 to 200,000 states: FP64 2,488
+// us, 1,785 on slices, FP32 1,898 and 884).  Kept for the next tail, which is
+// often of the same instances.  False when they cannot be had.
+constexpr int32_t kTailTileRows = 2048;  // rows a block orders (a wavefront per sort window)
+template <typename T>
+bool ensure_tail_slices(rp_context* ctx, rp_system* s, bool tr, const std::vector<int32_t>& who) {
+  rp_system::TailSlices<T>& ta = tail_slices_for<T>(s, tr);
+  if (ta.ss.ok && std::all_of(who.begin(), who.end(), [&](int32_t k) { return ta.lo[k] < ta.hi[k]; })) return true;
+  ta.ss.ok = false;
+  const int K = s->K;
+  ta.lo.assign(K, 0);
+  ta.hi.assign(K, 0);
+  rp_system::TileSet& ts = ta.ts;
+  std::vector<int32_t> row0, w0;
+  std::vector<int32_t>&nrows = ts.nrows_h, &nw = ts.nw_h, &inst = ts.inst_h, &inst0 = ts.inst0_h;
+  nrows.clear();
+  nw.clear();
+  inst.clear();
+  inst0.assign(K + 1, 0);
+  size_t next = 0;
+  for (int k = 0; k < K; k++) {
+    inst0[k] = (int32_t)row0.size();
+    if (next >= who.size() || who[next] != k) continue;
+    next++;
+    const int64_t lo = s->roff_h[k], hi = s->roff_h[k + 1];
+    for (int64_t r = lo; r < hi; r += kTailTileRows) {
+      row0.push_back((int32_t)r);
+      nrows.push_back((int32_t)std::min<int64_t>(kTailTileRows, hi - r));
+      inst.push_back(k);
+      w0.push_back((int32_t)lo);
+      nw.push_back((int32_t)(hi - lo));
+    }
+  }
+  const int32_t nt = (int32_t)row0.size();
+  inst0[K] = nt;
+  ts.kind_h.assign(nt, WIN_WHOLE);
+  std::vector<int32_t> t_s0;
+  const bool ok = if_memory_allows(ctx, [&] {
+    Uploads up(ctx);
+    for (DBuf<int32_t>* b : {&ts.row0, &ts.nrows, &ts.inst, &ts.w0, &ts.nw, &ts.kind}) dalloc(ctx, *b, (size_t)nt);
+    dalloc(ctx, ts.inst0, (size_t)K + 1);
+    up.add(ts.row0.p, row0.data(), (size_t)nt);
+    up.add(ts.nrows.p, nrows.data(), (size_t)nt);
+    up.add(ts.inst.p, inst.data(), (size_t)nt);
+    up.add(ts.inst0.p, inst0.data(), (size_t)K + 1);
+    up.add(ts.w0.p, w0.data(), (size_t)nt);
+    up.add(ts.nw.p, nw.data(), (size_t)nt);
+    up.add(ts.kind.p, ts.kind_h.data(), (size_t)nt);
+    up.run();
+    ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, 0};
+    return build_slices<T>(ctx, s, tr, ts, ta.ss, false, t_s0);
+  });
+  if (!ok) return false;
+  for (int32_t k : who) {
+    ta.lo[k] = t_s0[inst0[k]];
+    ta.hi[k] = t_s0[inst0[k + 1]];
+  }
   return true;
 }
 
@@ -1826,6 +1932,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
       int64_t j0 = launched;
       int32_t tail_tried = -1;  // done count at the last look at the tail
       bool tail = false;
+      Sliced<T> tail_slv{};
       // (ahead > 0 at max_iter: one more pass runs the check of those sweeps)
       while (launched < cfg.max_iter || ahead > 0) {
         const int64_t end = std::min<int64_t>(cfg.max_iter, j0 + batch);
@@ -1857,14 +1964,31 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
           const double* pl = ((launched - 1) & 1) ? P1 : P0;
           HIPCHK(ctx, launch_jacobi_check(st, tl, launched, pl, s->status_in.p, s->iters_in.p, s->meas_in.p,
                                           s->thr_in.p, cfg.strict, cfg.max_iter, ndone));
-          std::vector<int32_t> st_h((size_t)K), ts0_h;
+          std::vector<int32_t> st_h((size_t)K), lo, hi;
           to_host(ctx, st_h.data(), s->status_in.p, (size_t)K);
           if (std::none_of(st_h.begin(), st_h.end(), [](int32_t v) { return v == ST_RUN; })) break;
-          if (sl_on) {
-            ts0_h.resize((size_t)tl.ntile + 1);
-            to_host(ctx, ts0_h.data(), slv.t_s0, (size_t)tl.ntile + 1);
-          }
-          if (build_tail(ctx, s, sizeof(T), st_h, sweep_tiles<T>(s, ce_on), sl_on ? &ts0_h : nullptr)) {
+          const std::vector<int32_t> who = tail_instances(s, sizeof(T), st_h);
+          if (!who.empty()) {
+            if (ce_on && ensure_tail_slices<T>(ctx, s, tr, who)) {
+              const auto& ta = tail_slices_for<T>(s, tr);
+              tail_slv = ta.ss.v;
+              lo = ta.lo;
+              hi = ta.hi;
+            } else if (sl_on) {
+              const rp_system::TileSet& main = tiles_for<T>(s);
+              std::vector<int32_t> ts0_h((size_t)tl.ntile + 1);
+              to_host(ctx, ts0_h.data(), slv.t_s0, (size_t)tl.ntile + 1);
+              tail_slv = slv;
+              lo.assign(K, 0);
+              hi.assign(K, 0);
+              for (int32_t k : who) {
+                // (an instance's tiles have windows of one kind)
+                if (main.kind_h[main.inst0_h[k]] != WIN_WHOLE) continue;
+                lo[k] = ts0_h[main.inst0_h[k]];
+                hi[k] = ts0_h[main.inst0_h[k + 1]];
+              }
+            }
+            build_tail(ctx, s, who, lo, hi);
             tail = true;
             break;
           }
@@ -1885,7 +2009,7 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
           const int64_t j1 = launched;
           const int n = (int)std::min<int64_t>(kResidentSweeps, cfg.max_iter - launched);
           if (s->tail_sliced)
-            HIPCHK(ctx, launch_jacobi_resident_sliced<T>(st, slv, rhs, w.xa.p, w.xb.p, tt, s->tail_slo.p,
+            HIPCHK(ctx, launch_jacobi_resident_sliced<T>(st, tail_slv, rhs, w.xa.p, w.xb.p, tt, s->tail_slo.p,
                                                          s->tail_shi.p, launched, n, s->status_in.p, s->iters_in.p,
                                                          s->meas_in.p, s->thr_in.p, cfg.strict, cfg.max_iter, ndone,
                                                          cfg.measmode == MEAS_WDELTA));
