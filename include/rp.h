@@ -129,7 +129,11 @@ typedef struct rp_opts {
                             are too large for one LDS window and have no
                             band, cells: row sums in LDS, the iterate staged
                             panel by panel, each row summed in order (as by
-                            0 and 1; reported as lanes 0); otherwise tuned:
+                            0 and 1; reported as lanes 0; built on first use
+                            and kept with the system: 12 bytes per off-
+                            diagonal entry in FP64, 8 in FP32, for each
+                            direction; without that memory the system is
+                            solved on the other layouts); otherwise tuned:
                             sliced rows and the lane
                             counts from the mean row length and its two
                             neighbours are timed on a few sweeps the first

@@ -379,6 +379,21 @@ void dalloc(rp_context* ctx, DBuf<T>& b, size_t n) {
   }
 }
 
+// build(), which returns whether it succeeded, or false where the memory for it
+// cannot be had: what it builds is then done without.
+template <typename Build>
+bool if_memory_allows(rp_context* ctx, Build build) {
+  const std::string err = ctx->err;
+  try {
+    return build();
+  } catch (const Fail& f) {
+    if (f.code != RP_ERR_OOM) throw;
+    ctx->err = err;
+    (void)hipGetLastError();  // not for the next launch to report
+    return false;
+  }
+}
+
 void* pinned(rp_context* ctx, size_t bytes) {
   HIPCHK(ctx, ctx->pin.reserve(bytes));
   return ctx->pin.p;
@@ -1250,16 +1265,12 @@ template <>
 CellSet<float>& cells_for<float>(rp_system* s, bool tr) { return s->ce32[tr ? 1 : 0]; }
 
 // Cells of the forward or transposed matrix, built once; false when the
-// system's shape does not run on cells or the steps hold fewer than
-// kCellStepEntries entries each (a hub row's are taken one at a time).
+// system's shape does not run on cells, the steps hold fewer than
+// kCellStepEntries entries each (a hub row's are taken one at a time) or there
+// is no memory for them.
 constexpr int kCellStepEntries = 16;
 template <typename T>
-bool ensure_cells(rp_context* ctx, rp_system* s, bool tr) {
-  CellSet<T>& cs = cells_for<T>(s, tr);
-  rp_system::TileSet& ts = cell_tiles_for<T>(s);
-  if (!ts.ok || !s->tiles_on) return false;
-  if (cs.built) return cs.ok;
-  if (tr) ensure_transpose(ctx, s);
+bool build_cells(rp_context* ctx, rp_system* s, bool tr, const rp_system::TileSet& ts, CellSet<T>& cs) {
   const MatView<T> m = view<T>(s, tr);
   const DBuf<int32_t>& blk = sizeof(T) == 4 ? s->cblk32 : s->cblk64;
   const int64_t nlist = (int64_t)ts.tl.ntile * CELL_WAVES;
@@ -1271,7 +1282,6 @@ bool ensure_cells(rp_context* ctx, rp_system* s, bool tr) {
   HIPCHK(ctx, launch_cells_count<T>(ctx->stream, m, ts.tl, count.p, unit.p));
   HIPCHK(ctx, launch_scan(ctx->stream, count.p, base.p, nlist, scan_tmp.p));
   const int32_t nstep = read_i32(ctx, base.p + nlist);
-  cs.built = true;
   // (a step adds 64 entries, unless rows have many entries in one panel)
   if ((int64_t)nstep > s->z / kCellStepEntries) return false;
   dalloc(ctx, cs.step, (size_t)nstep);
@@ -1281,8 +1291,25 @@ bool ensure_cells(rp_context* ctx, rp_system* s, bool tr) {
   HIPCHK(ctx, launch_cells_fill<T>(ctx->stream, m, ts.tl, ts.order.p, base.p, unit.p, cs.step.p, cs.val.p, cs.ix.p,
                                    cs.rec.p));
   cs.v = Cells<T>{cs.rec.p, blk.p, cs.step.p, cs.val.p, cs.ix.p, m.d, (int32_t)blk.n - 1};
-  cs.ok = true;
   return true;
+}
+
+template <typename T>
+bool ensure_cells(rp_context* ctx, rp_system* s, bool tr) {
+  CellSet<T>& cs = cells_for<T>(s, tr);
+  const rp_system::TileSet& ts = cell_tiles_for<T>(s);
+  if (!ts.ok || !s->tiles_on) return false;
+  if (cs.built) return cs.ok;
+  if (tr) ensure_transpose(ctx, s);
+  cs.built = true;
+  cs.ok = if_memory_allows(ctx, [&] { return build_cells<T>(ctx, s, tr, ts, cs); });
+  if (!cs.ok) {
+    cs.step.release();
+    cs.val.release();
+    cs.ix.release();
+    cs.rec.release();
+  }
+  return cs.ok;
 }
 
 // Slice bytes above which a sweep streams them past the caches (the MI355X
@@ -1549,21 +1576,6 @@ template <>
 rp_system::TailSlices<double>& tail_slices_for<double>(rp_system* s, bool tr) { return s->tail64[tr ? 1 : 0]; }
 template <>
 rp_system::TailSlices<float>& tail_slices_for<float>(rp_system* s, bool tr) { return s->tail32[tr ? 1 : 0]; }
-
-// build(), which returns whether it succeeded, or false where the memory for it
-// cannot be had: what it builds is then done without.
-template <typename Build>
-bool if_memory_allows(rp_context* ctx, Build build) {
-  const std::string err = ctx->err;
-  try {
-    return build();
-  } catch (const Fail& f) {
-    if (f.code != RP_ERR_OOM) throw;
-    ctx->err = err;
-    (void)hipGetLastError();  // not for the next launch to report
-    return false;
-  }
-}
 
 // Sliced rows of the tail's instances, for sweeps that ran on cells: resident
 // sweeps on one lane per row wait for a long row's entries one after another
@@ -1836,10 +1848,11 @@ int64_t run_inner(rp_context* ctx, rp_system* s, bool tr, const T* rhs, const In
       HIPCHK(ctx, launch_stall(st, K, launched, s->status_in.p, s->iters_in.p, s->meas_in.p, s->sbest.p,
                                s->sbest_it.p, kStallWindow, ndone));
   };
-  // tiled sweeps on sliced rows when this call chose them
+  // tiled sweeps on cells or sliced rows when this call chose them (on sliced rows
+  // also where only the other precision's sweeps have cells)
   const bool ce_on = s->cells && tiled<T>(s) && ensure_cells<T>(ctx, s, tr);
   const Cells<T> cev = ce_on ? cells_for<T>(s, tr).v : Cells<T>{};
-  const bool sl_on = !ce_on && s->sliced && tiled<T>(s) && ensure_sliced<T>(ctx, s, tr);
+  const bool sl_on = !ce_on && (s->sliced || s->cells) && tiled<T>(s) && ensure_sliced<T>(ctx, s, tr);
   const Sliced<T> slv = sl_on ? sliced_for<T>(s, tr).v : Sliced<T>{};
   const int kJ = std::is_same<T, float>::value ? RP_PROF_JACOBI_FP32 : RP_PROF_JACOBI_FP64;
   const int kT = std::is_same<T, float>::value ? RP_PROF_JACOBI_TAIL_FP32 : RP_PROF_JACOBI_TAIL_FP64;
@@ -2218,10 +2231,13 @@ void refine(rp_context* ctx, rp_system* s, bool tr, int method, const double* b6
   while (true) {
     const bool t64 = tiled<double>(s);
     if (ctx->prof) to_host(ctx, sto.data(), s->status_out.p, K);
-    // sliced rows when this call uses them and the FP64 slices exist
+    // sliced rows or cells when this call uses them and theirs in FP64 exist.
+    // (Around FP32 solves they are not built for the residuals: cells cost 12 bytes
+    // per entry and 1.6 ms for 34 M entries, and save 0.13 ms of each of some ten
+    // residuals.)
     const SlicedSet<double>& sl64 = sliced_for<double>(s, tr);
     const CellSet<double>& ce64 = cells_for<double>(s, tr);
-    const bool on_cells = t64 && s->cells && ensure_cells<double>(ctx, s, tr);
+    const bool on_cells = t64 && s->cells && (std::is_same<T, double>::value ? ensure_cells<double>(ctx, s, tr) : ce64.ok);
     const Tiles& t64l = sweep_tiles<double>(s, on_cells).tl;
     if (on_cells)
       PROF(ctx, RP_PROF_RESIDUAL_FP64,
