@@ -274,6 +274,7 @@ struct rp_system {
   // per value width: FP64 windows use a whole LDS, FP32 windows half of it
   struct TileSet {
     bool ok = false;
+    bool planned = false;  // cells: `ok` says whether they pay
     DBuf<int32_t> row0, nrows, inst, inst0, w0, nw, kind, order;
     std::vector<uint8_t> whole_h;  // per instance: window kind WIN_WHOLE (16-bit columns)
     std::vector<int32_t> nrows_h;  // rows per tile
@@ -287,8 +288,8 @@ struct rp_system {
   SlicedSet<double> sl64[2];
   SlicedSet<float> sl32[2];
   bool sliced = false;  // per call: tiled sweeps use the sliced rows
-  // cells: their own tiles (built where cells_pay), and the entries of the
-  // forward [0] and transposed [1] matrix
+  // cells: their own tiles (planned by the first solve of that precision), and
+  // the entries of the forward [0] and transposed [1] matrix
   TileSet c64, c32;  // order: the tiles of the blocks' lists one after another
   DBuf<int32_t> cblk64, cblk32;  // lists of the blocks: [cblk[b], cblk[b+1]) of order
   CellSet<double> ce64[2];
@@ -1028,6 +1029,14 @@ CellPlan cell_plan(const rp_system* s, int cus, size_t width, int64_t most) {
   return p;
 }
 
+constexpr int64_t kCellRowsLeast = CELL_ROWS / 2;  // most rows per tile of the finest plan
+
+int32_t most_cell_tiles(const rp_system* s) {
+  int64_t n = 0;
+  for (int k = 0; k < s->K; k++) n += (s->roff_h[k + 1] - s->roff_h[k] + kCellRowsLeast - 1) / kCellRowsLeast;
+  return (int32_t)n;
+}
+
 // Whether the sweeps of values `width` bytes wide run on cells, and their
 // tiles.  The other layouts take 2.5 ns (FP64) or 1.7 ns (FP32) of a compute
 // unit per entry of an instance without a window (a gather from L2 each) and
@@ -1036,11 +1045,10 @@ CellPlan cell_plan(const rp_system* s, int cus, size_t width, int64_t most) {
 // banded instances, whose entries fall into few panels.  The rows per tile are
 // those of the shortest modelled sweep: fewer rows even out the blocks' lists,
 // more rows stage fewer panels.
-void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBuf<int32_t>& blk,
+bool build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBuf<int32_t>& blk,
                       const rp_system::TileSet& main, size_t width, Uploads& up) {
   const int K = s->K;
-  ts.ok = false;
-  if (s->npad <= 0 || !main.ok || ctx->cus < 8) return;
+  if (s->npad <= 0 || !main.ok || ctx->cus < 8) return false;
   const int64_t pw = width == 4 ? cell_panel<float>() : cell_panel<double>();
   double other = 0.0;
   bool none = false;
@@ -1048,18 +1056,18 @@ void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBu
     const int64_t rows = s->roff_h[k + 1] - s->roff_h[k];
     if (rows == 0) continue;
     const int32_t kind = main.kind_h[main.inst0_h[k]];
-    if (kind == WIN_BAND || rows >= pw << (30 - CELL_STEP_BITS)) return;
+    if (kind == WIN_BAND || rows >= pw << (30 - CELL_STEP_BITS)) return false;
     none = none || kind == WIN_NONE;
     const double ns = kind == WIN_NONE ? (width == 4 ? 1.7 : 2.5) : (width == 4 ? 0.57 : 1.05);
     other += 1e-3 * ns * (double)s->z_h[k] / (double)ctx->cus;
   }
-  if (!none) return;
+  if (!none) return false;
   CellPlan plan;
-  for (int64_t most = CELL_ROWS; most >= CELL_ROWS / 2; most -= 1024) {
+  for (int64_t most = CELL_ROWS; most >= kCellRowsLeast; most -= 1024) {
     CellPlan p = cell_plan(s, ctx->cus, width, most);
     if (plan.per.empty() || p.time < plan.time) plan = std::move(p);
   }
-  if (plan.time > 0.9 * other) return;
+  if (plan.time > 0.9 * other) return false;
   std::vector<int32_t> trow0, tnr, tinst, tw0, tnw, tkind, tc0(K + 1, 0);
   for (int k = 0; k < K; k++) {
     tc0[k] = (int32_t)trow0.size();
@@ -1096,7 +1104,7 @@ void build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBu
   ts.kind_h = tkind;
   ts.inst0_h = tc0;
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, 0};
-  ts.ok = true;
+  return true;
 }
 
 // Resident Jacobi (one block per instance, many sweeps per launch) pays off
@@ -1297,8 +1305,18 @@ bool build_cells(rp_context* ctx, rp_system* s, bool tr, const rp_system::TileSe
 template <typename T>
 bool ensure_cells(rp_context* ctx, rp_system* s, bool tr) {
   CellSet<T>& cs = cells_for<T>(s, tr);
-  const rp_system::TileSet& ts = cell_tiles_for<T>(s);
-  if (!ts.ok || !s->tiles_on) return false;
+  rp_system::TileSet& ts = cell_tiles_for<T>(s);
+  if (!s->tiles_on) return false;
+  if (!ts.planned) {
+    ts.planned = true;
+    ts.ok = if_memory_allows(ctx, [&] {
+      Uploads up(ctx);
+      const bool pay = build_cell_tiles(ctx, s, ts, sizeof(T) == 4 ? s->cblk32 : s->cblk64, tiles_for<T>(s), sizeof(T), up);
+      up.run();
+      return pay;
+    });
+  }
+  if (!ts.ok) return false;
   if (cs.built) return cs.ok;
   if (tr) ensure_transpose(ctx, s);
   cs.built = true;
@@ -2857,10 +2875,12 @@ void assemble_system(rp_context* ctx, rp_system* s, const rp_chain* chain, int32
   build_tiles(ctx, s, s->t32, sizeof(float), 2, hist, up);
   build_resident(ctx, s, s->res64, sizeof(double), up);
   build_resident(ctx, s, s->res32, sizeof(float), up);
-  build_cell_tiles(ctx, s, s->c64, s->cblk64, s->t64, sizeof(double), up);
-  build_cell_tiles(ctx, s, s->c32, s->cblk32, s->t32, sizeof(float), up);
-  for (const rp_system::TileSet* t : {&s->t64, &s->t32, &s->c64, &s->c32})
-    if (t->ok) s->ntile_max = std::max(s->ntile_max, t->tl.ntile);
+  for (const rp_system::TileSet* t : {&s->t64, &s->t32}) {
+    if (!t->ok) continue;
+    s->ntile_max = std::max(s->ntile_max, t->tl.ntile);
+    if (std::find(t->kind_h.begin(), t->kind_h.end(), WIN_NONE) != t->kind_h.end())
+      s->ntile_max = std::max(s->ntile_max, most_cell_tiles(s));
+  }
   up.run();
   HIPCHK(ctx, hipStreamSynchronize(st));
 }
