@@ -51,7 +51,7 @@ def pmc_traffic(kernel_id, kernel_name=None, workload=None):
     and WRITE_SIZE runs (scaled by a plain copy of known size), or None when
     the kernel sources changed since the counters were taken, the counters
     were taken on another workload, or they are of another kernel than
-    kernel_name (a name, name prefix or prefixes: another row layout)."""
+    kernel_name (a name or name prefix: another row layout)."""
     try:
         with open(PMC_FILE) as f:
             d = json.load(f)
@@ -506,7 +506,8 @@ def main():
     out_extra = {}
     if not args.no_extras:
         out_extra = extras(args, chain, ctx, rows, step, times, seed_v, dev, rp, B, x, rowp, col, val, goal, off, cls)
-    roof, kernels = roofline(prof, {k: v[0]["lanes"] for k, v in last.items()}, chain.name, args.schedule)
+    roof, kernels = roofline(prof, {k: "cells" if v[0]["cells"] else v[0]["lanes"] for k, v in last.items()},
+                             chain.name)
 
     out = {
         "metric": METRIC, "value": round(value, 3), "unit": "solves/s", "n_gpus": 1, "steps": args.steps,
@@ -533,20 +534,19 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-def sweep_kernel(kernel_id, lanes, schedule=-1):
-    """Name (prefix, or prefixes) of the Jacobi sweep kernel a solve ran, from its
-    reported layout (0: cells or, always with schedule 0, sliced rows; L > 0: L
-    lanes per row), as the profilers print it."""
+def sweep_kernel(kernel_id, layout):
+    """Name (or name prefix) of the Jacobi sweep kernel a solve ran, from its
+    reported layout ("cells", 0: sliced rows, L > 0: L lanes per row), as the
+    profilers print it."""
     t = {"jacobi_fp64": "double", "jacobi_fp32": "float"}.get(kernel_id)
-    if t is None or lanes is None:
+    if t is None or layout is None:
         return None
-    if lanes != 0:
-        return f"rpk::k_jacobi_tile<{t}, {lanes}>"
-    sliced = f"rpk::k_jacobi_sliced<{t},"
-    return sliced if schedule == 0 else (f"rpk::k_jacobi_cells<{t}>", sliced)
+    if layout == "cells":
+        return f"rpk::k_jacobi_cells<{t}>"
+    return f"rpk::k_jacobi_sliced<{t}," if layout == 0 else f"rpk::k_jacobi_tile<{t}, {layout}>"
 
 
-def roofline(prof, layouts=None, workload=None, schedule=-1):
+def roofline(prof, layouts=None, workload=None):
     """Roofline entry for the kernel with the most time, from the library's
     event timing: algorithmic bytes / summed time over the timed steps.
     layouts: lanes reported per solve row (selects the kernel whose byte
@@ -564,7 +564,7 @@ def roofline(prof, layouts=None, workload=None, schedule=-1):
     roof = {"bound": "hbm", "kernel": dom, "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4),
             "traffic": pmc_traffic(dom, sweep_kernel(dom, (layouts or {}).get(
-                {"jacobi_fp64": "jacobi_fp64", "jacobi_fp32": "jacobi_fp32r"}.get(dom, dom)), schedule), workload),
+                {"jacobi_fp64": "jacobi_fp64", "jacobi_fp32": "jacobi_fp32r"}.get(dom, dom))), workload),
             "launches": n, "avg_launch_us": round(1000 * ms / n, 3), "alg_bytes_per_launch": b / n}
     return roof, kernels
 

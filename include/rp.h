@@ -129,7 +129,7 @@ typedef struct rp_opts {
                             are too large for one LDS window and have no
                             band, cells: row sums in LDS, the iterate staged
                             panel by panel, each row summed in order (as by
-                            0 and 1; reported as lanes 0; built on first use
+                            0 and 1; reported as cells; built on first use
                             and kept with the system: 12 bytes per off-
                             diagonal entry in FP64, 8 in FP32, for each
                             direction; without that memory the system is
@@ -189,11 +189,11 @@ typedef struct rp_solve_info {  /* one per instance */
                              of ||(I-A)^{-1}1|| has been computed              */
     int32_t status;       /* RP_OK or RP_ERR_* for this instance               */
     int32_t lanes;        /* layout the tiled sparse products used: lanes per
-                             row, or 0 for sliced rows and cells               */
+                             row, or 0 for sliced rows and cells (see cells)   */
     int32_t panels;       /* sliced rows only: column panels the instance's
                              iterate was staged in (its block is too large for
                              one LDS window and has no band), 0 otherwise     */
-    int32_t reserved;     /* 0                                                 */
+    int32_t cells;        /* 1 when the tiled sparse products ran on cells, else 0 */
 } rp_solve_info;
 
 typedef struct rp_context rp_context;

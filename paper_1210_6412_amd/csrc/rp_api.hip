@@ -2189,6 +2189,7 @@ struct SolveLog {
   std::vector<double> delta, resid, bound;
   std::vector<int32_t> status;  // device status codes (ST_*)
   int32_t lanes = 0;             // lanes per row of the sparse products
+  int32_t cells = 0;             // 1: on cells
   std::vector<int32_t> panels;   // per instance: column panels of its sliced rows (0: none)
   explicit SolveLog(int K)
       : iters(K, 0), refinements(K, 0), delta(K, 0.0), resid(K, 0.0), bound(K, -1.0), status(K, ST_RUN) {}
@@ -2590,6 +2591,8 @@ void solve_core(rp_context* ctx, rp_system* s, bool tr, int method, const double
   s->sliced = layout == 0;
   if (layout > 0) s->L = layout;
   log.lanes = s->sliced || s->cells ? 0 : s->L;
+  // (the paper's rule sweeps in FP64 whatever the precision asked for)
+  log.cells = s->cells && (!f32 || o.stop != RP_STOP_DELTA || ensure_cells<double>(ctx, s, tr)) ? 1 : 0;
   log.panels.assign(K, 0);
   if (s->sliced) {
     const std::vector<int32_t>& np = f32 ? sliced_for<float>(s, tr).npan_h : sliced_for<double>(s, tr).npan_h;
@@ -2899,7 +2902,7 @@ int finish(rp_context* ctx, rp_system* s, const SolveLog& log, rp_solve_info* in
       info[k].status = code;
       info[k].lanes = log.lanes;
       info[k].panels = log.panels.empty() ? 0 : log.panels[k];
-      info[k].reserved = 0;
+      info[k].cells = log.cells;
     }
   }
   if (worst != RP_OK) {
