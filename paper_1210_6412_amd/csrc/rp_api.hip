@@ -16,6 +16,7 @@
 #include <deque>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -275,6 +276,9 @@ struct rp_system {
   struct TileSet {
     bool ok = false;
     bool planned = false;  // cells: `ok` says whether they pay
+    // cells: the blocks' lists (order_h[blk_h[b] .. blk_h[b+1])), time of the longest
+    std::vector<int32_t> order_h, blk_h;
+    double time = 0.0;
     DBuf<int32_t> row0, nrows, inst, inst0, w0, nw, kind, order;
     std::vector<uint8_t> whole_h;  // per instance: window kind WIN_WHOLE (16-bit columns)
     std::vector<int32_t> nrows_h;  // rows per tile
@@ -1103,6 +1107,9 @@ bool build_cell_tiles(rp_context* ctx, rp_system* s, rp_system::TileSet& ts, DBu
   up.add(ts.order.p, plan.order.data(), (size_t)nt);
   ts.kind_h = tkind;
   ts.inst0_h = tc0;
+  ts.order_h = plan.order;
+  ts.blk_h = plan.first;
+  ts.time = plan.time;
   ts.tl = Tiles{ts.row0.p, ts.nrows.p, ts.inst.p, ts.inst0.p, ts.w0.p, ts.nw.p, ts.kind.p, nt, K, 0};
   return true;
 }
@@ -1273,10 +1280,13 @@ template <>
 CellSet<float>& cells_for<float>(rp_system* s, bool tr) { return s->ce32[tr ? 1 : 0]; }
 
 // Cells of the forward or transposed matrix, built once; false when the
-// system's shape does not run on cells, the steps hold fewer than
-// kCellStepEntries entries each (a hub row's are taken one at a time) or there
-// is no memory for them.
-constexpr int kCellStepEntries = 16;
+// system's shape does not run on cells, when their steps would take longer than
+// the plan's sweep, or when there is no memory for them.  A step adds up to 64
+// entries of different rows; those of a row with many entries in a panel are taken
+// one at a time, kCellStep us each (28 chains of 60,000 states, one row of 20,000
+// entries in one of them: FP64 53 -> 2,764 us per sweep, four lanes per row 848;
+// rows of 300 in all: 82 on cells, 90 on lanes; FP32 75 and 71).
+constexpr double kCellStep = 0.135;
 template <typename T>
 bool build_cells(rp_context* ctx, rp_system* s, bool tr, const rp_system::TileSet& ts, CellSet<T>& cs) {
   const MatView<T> m = view<T>(s, tr);
@@ -1289,9 +1299,18 @@ bool build_cells(rp_context* ctx, rp_system* s, bool tr, const rp_system::TileSe
   dalloc(ctx, unit, (size_t)ts.tl.ntile);
   HIPCHK(ctx, launch_cells_count<T>(ctx->stream, m, ts.tl, count.p, unit.p));
   HIPCHK(ctx, launch_scan(ctx->stream, count.p, base.p, nlist, scan_tmp.p));
-  const int32_t nstep = read_i32(ctx, base.p + nlist);
-  // (a step adds 64 entries, unless rows have many entries in one panel)
-  if ((int64_t)nstep > s->z / kCellStepEntries) return false;
+  std::vector<int32_t> steps((size_t)nlist);
+  to_host(ctx, steps.data(), count.p, (size_t)nlist);
+  int64_t nstep = 0;
+  for (size_t b = 0; b + 1 < ts.blk_h.size(); b++) {
+    int64_t longest = 0;  // steps of the block's tiles one after another
+    for (int32_t i = ts.blk_h[b]; i < ts.blk_h[b + 1]; i++) {
+      const int32_t* of = steps.data() + (size_t)ts.order_h[i] * CELL_WAVES;
+      longest += *std::max_element(of, of + CELL_WAVES);
+      nstep = std::accumulate(of, of + CELL_WAVES, nstep);
+    }
+    if (kCellStep * (double)longest > ts.time) return false;
+  }
   dalloc(ctx, cs.step, (size_t)nstep);
   dalloc(ctx, cs.val, (size_t)s->z + 1);
   dalloc(ctx, cs.ix, (size_t)s->z + 1);

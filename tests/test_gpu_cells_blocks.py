@@ -8,8 +8,8 @@ residual that one inner solve reaches (no FP64 residual enters the iterate then)
 BiCGStab and the adjoint are held to the oracle within 1e-10, the certificate's own
 bound.
 
-The second batch has the shape of cells, but a row of 20,000 entries in every chain,
-whose entries would be taken one at a time: its forward products stay off the cells,
+The second batch has the shape of cells, but a row of 20,000 entries in one chain or
+in every one, whose entries would be taken one at a time: its forward products stay off the cells,
 its transposed ones do not."""
 import numpy as np
 import pytest
@@ -103,8 +103,10 @@ def _hub(n, width, seed):
 
 
 @pytest.mark.parametrize("precision", [rp.RP_FP64, rp.RP_FP32_REFINED])
-def test_hub_rows_stay_off_the_cells(precision):
-    parts = [_hub(60_000 - 37 * i, 20_000, SEED + 100 + i) for i in range(28)]
+@pytest.mark.parametrize("hubs", [1, 28])
+def test_hub_rows_stay_off_the_cells(hubs, precision):
+    plain = [cg.random_sparse(60_000 - 37 * i, 1, 8, 0.05, 0.05, seed=SEED + 100 + i) for i in range(4)]
+    parts = [_hub(60_000 - 37 * i, 20_000, SEED + 100 + i) if i < hubs else plain[i % 4] for i in range(28)]
     c = cg.concat(parts, name="hubs")
     G.banner(f"cells, hub rows: n={c.n} nnz={c.nnz}")
     sys = G.precompute(c)[0]
