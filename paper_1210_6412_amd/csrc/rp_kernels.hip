@@ -1234,10 +1234,11 @@ struct RowBatch {
 };
 
 // One wavefront per row: lane l takes the entries 2l, 2l+1 (+ 128 j) of the row,
-// both with one load (at any alignment).  A pair that reaches past the row's end
-// is moved back onto its last two entries (the arrays have spare elements for a
-// matrix of one entry); what is then not the lane's own counts as value 0 at
-// column 0 of the window.
+// both with one load (at any alignment).  The last run of fewer than 128 entries is
+// held apart: a pair that reaches past the row's end is moved back onto its last two
+// entries (the arrays have spare elements for a matrix of one entry), and what is
+// then not the lane's own is left out of its sum, not added as 0 x, as x may not be
+// finite.
 template <typename T, int U, int J>
 struct RowBatch<T, 64, U, J> {
   using Val = T __attribute__((ext_vector_type(2), aligned(alignof(T))));
@@ -1246,11 +1247,9 @@ struct RowBatch<T, 64, U, J> {
   static constexpr int P = J / 2;
   int k0[U], k1[U];
   T bi[U], di[U];
-  Val vv[U][P];
-  Col cc[U][P];      // not used with 16-bit columns
-  Col16 hh[U][P];
-
-  __device__ __forceinline__ static int first(int k, int k1) { return max(min(k, k1 - 2), 0); }
+  Val vv[U][P + 1];  // [P]: the last run
+  Col cc[U][P + 1];  // not used with 16-bit columns
+  Col16 hh[U][P + 1];
 
   template <int KIND>
   __device__ __forceinline__ void load(const MatView<T>& m, const T* __restrict__ rhs, int r0, int nr, int base, int g,
@@ -1265,32 +1264,32 @@ struct RowBatch<T, 64, U, J> {
       di[u] = r < end ? m.d[r] : (T)1;
     }
 #pragma unroll
-    for (int u = 0; u < U; u++)
+    for (int u = 0; u < U; u++) {
 #pragma unroll
-      for (int j = 0; j < P; j++) {
+      for (int j = 0; j <= P; j++) {
         vv[u][j] = (Val)(T)0;
         cc[u][j] = (Col)0;
         hh[u][j] = (Col16)(uint16_t)0;
-        if (k0[u] + j * 128 < k1[u]) read<KIND>(m, k0[u] + 2 * lane + j * 128, k1[u], vv[u][j], cc[u][j], hh[u][j]);
       }
+#pragma unroll
+      for (int j = 0; j < P; j++)
+        if (k0[u] + (j + 1) * 128 <= k1[u]) read<KIND>(m, k0[u] + 2 * lane + j * 128, vv[u][j], cc[u][j], hh[u][j]);
+      if (last(u) < k1[u]) read<KIND>(m, max(min(last(u) + 2 * lane, k1[u] - 2), 0), vv[u][P], cc[u][P], hh[u][P]);
+    }
+  }
+  // first entry of row u's last run
+  __device__ __forceinline__ int last(int u) const { return k1[u] - ((k1[u] - k0[u]) & 127); }
+  template <int KIND>
+  __device__ __forceinline__ static void read(const MatView<T>& m, int k, Val& v, Col& c, Col16& h) {
+    v = *reinterpret_cast<const Val*>(m.val + k);
+    if (KIND == WIN_WHOLE) h = *reinterpret_cast<const Col16*>(m.c16 + k);
+    else c = *reinterpret_cast<const Col*>(m.col + k);
   }
   template <int KIND>
-  __device__ __forceinline__ static void read(const MatView<T>& m, int k, int k1, Val& v, Col& c, Col16& h) {
-    const int kk = first(k, k1);
-    v = *reinterpret_cast<const Val*>(m.val + kk);
-    if (KIND == WIN_WHOLE) h = *reinterpret_cast<const Col16*>(m.c16 + kk);
-    else c = *reinterpret_cast<const Col*>(m.col + kk);
-  }
-  // sum of the pair at k
-  template <int KIND>
-  __device__ __forceinline__ static T pair(const T* __restrict__ xs, const T* __restrict__ xg, int nw, int w0, int k,
-                                           int k1, Val v, Col c, Col16 h, T acc) {
-    const int c0 = KIND == WIN_WHOLE ? (int)h.x : c.x - w0, c1 = KIND == WIN_WHOLE ? (int)h.y : c.y - w0;
-    const bool in = k < k1, both = k + 1 < k1, back = k > 0 && !both;  // moved back: the lane's entry is the second
-    const T x0 = xget<KIND>(xs, xg, in ? (back ? c1 : c0) : 0, nw, w0), x1 = xget<KIND>(xs, xg, both ? c1 : 0, nw, w0);
-    acc += (in ? (back ? v.y : v.x) : (T)0) * x0;
-    acc += (both ? v.y : (T)0) * x1;
-    return acc;
+  __device__ __forceinline__ static T pair(const T* __restrict__ xs, const T* __restrict__ xg, int nw, int w0, Val v,
+                                           Col c, Col16 h, T acc) {
+    acc += v.x * xget<KIND>(xs, xg, KIND == WIN_WHOLE ? (int)h.x : c.x - w0, nw, w0);
+    return acc + v.y * xget<KIND>(xs, xg, KIND == WIN_WHOLE ? (int)h.y : c.y - w0, nw, w0);
   }
 
   // row sum of A_off times x for row u (valid in every lane)
@@ -1300,17 +1299,28 @@ struct RowBatch<T, 64, U, J> {
     T acc = 0;
 #pragma unroll
     for (int j = 0; j < P; j++)
-      if (k0[u] + j * 128 < k1[u])
-        acc = pair<KIND>(xs, xg, nw, w0, k0[u] + 2 * lane + j * 128, k1[u], vv[u][j], cc[u][j], hh[u][j], acc);
-    for (int k = k0[u] + P * 128; k < k1[u]; k += 4 * 128) {
+      if (k0[u] + (j + 1) * 128 <= k1[u]) acc = pair<KIND>(xs, xg, nw, w0, vv[u][j], cc[u][j], hh[u][j], acc);
+    for (int k = k0[u] + P * 128; k + 128 <= k1[u]; k += 4 * 128) {
       Val v[4];
       Col c[4];
       Col16 h[4];
 #pragma unroll
-      for (int j = 0; j < 4; j++) read<KIND>(m, k + 2 * lane + j * 128, k1[u], v[j], c[j], h[j]);
+      for (int j = 0; j < 4; j++)
+        if (k + (j + 1) * 128 <= k1[u]) read<KIND>(m, k + 2 * lane + j * 128, v[j], c[j], h[j]);
 #pragma unroll
       for (int j = 0; j < 4; j++)
-        acc = pair<KIND>(xs, xg, nw, w0, k + 2 * lane + j * 128, k1[u], v[j], c[j], h[j], acc);
+        if (k + (j + 1) * 128 <= k1[u]) acc = pair<KIND>(xs, xg, nw, w0, v[j], c[j], h[j], acc);
+    }
+    if (last(u) < k1[u]) {
+      const Val v = vv[u][P];
+      const int c0 = KIND == WIN_WHOLE ? (int)hh[u][P].x : cc[u][P].x - w0;
+      const int c1 = KIND == WIN_WHOLE ? (int)hh[u][P].y : cc[u][P].y - w0;
+      const int k = last(u) + 2 * lane;
+      const bool in = k < k1[u], both = k + 1 < k1[u], back = k > 0 && !both;  // moved back: its entry is the second
+      const T a0 = acc + (back ? v.y : v.x) * xget<KIND>(xs, xg, in ? (back ? c1 : c0) : 0, nw, w0);
+      acc = in ? a0 : acc;
+      const T a1 = acc + v.y * xget<KIND>(xs, xg, both ? c1 : 0, nw, w0);
+      acc = both ? a1 : acc;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
