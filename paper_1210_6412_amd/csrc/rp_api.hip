@@ -1370,10 +1370,11 @@ int32_t sort_window(const rp_system* s) {
 // per product: 24.4 and 23.0 narrow, 19.8 and 19.3 wide; one chain of 1.76 M states
 // 79 and 77 per sweep; the band of a 2 M-state program graph 22.4 and 26.3).
 constexpr int kNarrowSlots = 4;
-// Slices per tile up to which a wavefront has few (two on average).  Program graphs,
-// us per FP64 sweep, few / narrow shape: 60,000 states 6.8 / 7.3, 276,253 (17 slices
-// per tile) 8.0 / 10.1, 500,000 (31) 9.7 / 11.1, 1 M (61) 16.2 / 14.6; FP32 232,672
-// states (7) 9.0 / 9.2, 404,694 9.6 / 9.9, 800,000 (25) 11.3 / 11.3.
+// Slices of a slice's tile, on average, up to which a wavefront has few (two).
+// Program graphs, us per sweep, few / narrow shape: FP64 60,000 states 6.8 / 7.3,
+// 276,253 (17 slices per tile) 8.0 / 10.1, 500,000 (31) 9.7 / 11.1, 1 M (61) 16.2 /
+// 14.6; FP32 232,672 states (7) 9.0 / 9.2, 404,694 9.6 / 9.9, 800,000 (25) 11.3 /
+// 11.3.
 constexpr int kFewSlices = 2 * TNT / 64;
 
 // Sliced rows of a tile set and the forward or transposed matrix: a block per
@@ -1569,8 +1570,10 @@ bool build_slices(rp_context* ctx, rp_system* s, bool tr, const rp_system::TileS
                              (double)pent * (double)(sizeof(T) + 2) + (double)ncnt;
   ss.v.stream = slice_bytes > kStreamBytes ? 1 : 0;
   const bool narrow = total < (int64_t)kNarrowSlots * SLICE * nslice;
+  int64_t of_tile = 0;  // slices of a slice's tile, summed over the slices
+  for (int32_t t = 0; t < nt; t++) of_tile += (int64_t)(t_s0[t + 1] - t_s0[t]) * (t_s0[t + 1] - t_s0[t]);
   if (npaneled > 0) ss.v.shape = SLICES_WIDE;
-  else if (!ss.v.stream && nslice <= kFewSlices * nt && (sizeof(T) == 8 || narrow)) ss.v.shape = SLICES_FEW;
+  else if (!ss.v.stream && of_tile <= kFewSlices * (int64_t)nslice && (sizeof(T) == 8 || narrow)) ss.v.shape = SLICES_FEW;
   else ss.v.shape = narrow && (sizeof(T) == 4 || any_band) ? SLICES_NARROW : SLICES_WIDE;
   if (npaneled > 0) {
     HIPCHK(ctx, hipMemsetAsync(ss.val.p + (total + pent), 0, sizeof(T) * PANEL_SLACK, st));
@@ -1616,9 +1619,9 @@ rp_system::TailSlices<float>& tail_slices_for<float>(rp_system* s, bool tr) { re
 
 // Sliced rows of the tail's instances, for sweeps that ran on cells: resident
 // sweeps on one lane per row wait for a long row's entries one after another
-// (256 sweeps of the last chains of 256 with 1,000 to 200,000 states: FP64 2,488
-// us, 1,785 on slices, FP32 1,898 and 884).  Kept for the next tail, which is
-// often of the same instances.  False when they cannot be had.
+// (256 sweeps of the last chains of 256 with 1,000 to 200,000 states, one lane per
+// row -> slices: FP64 937 -> 774 us, FP32 350 -> 291).  Kept for the next tail, which
+// is often of the same instances.  False when they cannot be had.
 constexpr int32_t kTailTileRows = 2048;  // rows a block orders (a wavefront per sort window)
 template <typename T>
 bool ensure_tail_slices(rp_context* ctx, rp_system* s, bool tr, const std::vector<int32_t>& who) {

@@ -1127,10 +1127,10 @@ constexpr int kNoEntry = INT_MIN;
 // With one wavefront per row (rows of hundreds of entries) a batch holds up to
 // J x 64 entries of a row, two neighbours per lane and load, and the first row's
 // loads are issued before the x window is staged.  8,192 states with 820 entries
-// per row, us per sweep: FP64 25.3 -> 18.6, FP32 22.3 -> 15.9 (four entries per
-// lane, one per load, after the window, before); a plain sum over as many bytes
-// (67 MB, out of the last-level cache) takes 18.6, so the cache's rate and the
-// launch bound it now.  Two rows per wavefront at once were slower (20.9: 128
+// per row, us per sweep: FP64 25.3 -> 17.6, FP32 22.3 -> 15.1 (four entries per
+// lane, one per load, after the window, before; 18.0 and 15.4 with the last run's
+// selects on every one); a plain sum over as many bytes (67 MB, out of the last-level
+// cache) takes 18.6, so the cache's rate and the launch bound it now.  Two rows per wavefront at once were slower (20.9: 128
 // VGPRs and spills), and so were 32 lanes per row (25.4).  With shorter rows the
 // window's loads, which wait for those before them, came later instead (two and
 // four lanes per row: up to 60% slower), so they keep the order.
@@ -3435,9 +3435,9 @@ template hipError_t launch_spmv_sliced<float>(hipStream_t, int, Sliced<float>, c
 // LDS panel by panel.  For instances that fit no window and have no band.
 //
 // Without a window every entry gathers its x element from L2, a 128-byte line
-// for 8 bytes: 2.4 cycles of a compute unit's L1 per gather at best (257 G
-// gathers/s over the chip, measured), and the sliced sweep, one pass of a block
-// over its tile, adds the gathers' time to that of streaming the entries.  Here
+// for 8 bytes, and the sliced sweep, one pass of a block over its tile, adds the
+// gathers' time to that of streaming the entries (2.5 ns of a compute unit per FP64
+// entry on 8 M states, 1.05 with a whole window).  Here
 // a tile reads each line of its instance's x once, as part of a panel, whatever
 // the number of its entries; the entries stream meanwhile.  8 M states in chains
 // of 50,000 / 100,000 / 200,000 (us per sweep, sliced rows -> cells): FP64
